@@ -21,6 +21,7 @@
 
 #include "fr_device.h"
 #include "fr_kernels.h"
+#include "mf4.h"
 
 namespace fr {
 
@@ -1043,7 +1044,6 @@ __global__ void __launch_bounds__(NT_)
     }
     return;
   }
-  if constexpr (PL && !SAA) lds_barrier();  // every edge point has read its fields
   // phase 4b: triangle-plane interpolation of the 20 fields to the triangle
   // quadrature points (first factor of M7 / M10): one (field, plane) per
   // thread, its N_t values in registers, operator entries read from the LDS
@@ -1522,6 +1522,10 @@ __global__ void __launch_bounds__(NT_)
   }
 }
 
+}  // namespace fr
+#include "prism_volume_mf.h"
+namespace fr {
+
 // ------------------------------------------------------------ host side
 template <int P, typename R>
 static PrismOps<P, R> make_prism_ops(const HostOps& h) {
@@ -1594,19 +1598,27 @@ static void pack_disu(const RefElem& r, PrismDisuTab<P>* o) {
     }
 }
 
+// byte offset of the matrix-core table (single precision) behind the disu table
+template <int P, typename R>
+constexpr size_t prism_mf_offset() {
+  return (prism_disu_offset<P, R>() + sizeof(PrismDisuTab<P>) + 255) / 256 * 256;
+}
+
 template <int P, typename R>
 static size_t prism_bytes_t() {
-  return prism_disu_offset<P, R>() + sizeof(PrismDisuTab<P>);
+  return prism_mf_offset<P, R>() + (sizeof(R) == 4 ? PrismMfTab<P>::size * sizeof(float) : 0);
 }
 
 template <int P, typename R>
 static void prism_pack_t(const RefElem& r, void* dst) {
   pack_tri<P, R>(r.tri, (PrismTri<P, R>*)dst);
   pack_disu<P>(r, (PrismDisuTab<P>*)((char*)dst + prism_disu_offset<P, R>()));
+  if constexpr (sizeof(R) == 4) prism_mf_pack<P>(r, (float*)((char*)dst + prism_mf_offset<P, R>()));
 }
 
 // the device table of one order and precision: the prism operators in the
-// working precision, then the double-precision disu operators
+// working precision, the double-precision disu operators, and in single
+// precision the packed operators of the matrix-core volume kernel
 size_t prism_ops_bytes(int p, int prec) {
   const bool d = prec == 0;
   switch (p) {
@@ -1628,7 +1640,10 @@ void prism_ops_pack(const RefElem& r, int prec, void* dst) {
   }
 }
 
-// launch shapes of the volume kernel: two threads per quadrature column
+// Launch shapes of the vector volume kernel: two threads per quadrature
+// column.  It runs double precision, and in single precision what the
+// matrix-core kernel (PrismMf) does not cover: no flux anti-aliasing, and
+// surface-flux anti-aliasing.
 template <int P, bool DBL>
 struct PrismLaunch;
 template <> struct PrismLaunch<1, false> { static constexpr int EB = 8, NT = 64; };   // 64 column threads
@@ -1640,6 +1655,12 @@ template <> struct PrismLaunch<1, true> { static constexpr int EB = 8, NT = 64; 
 template <> struct PrismLaunch<2, true> { static constexpr int EB = 3, NT = 64; };    // 54
 template <> struct PrismLaunch<3, true> { static constexpr int EB = 2, NT = 64; };    // 64
 template <> struct PrismLaunch<4, true> { static constexpr int EB = 1, NT = 64; };    // 50
+
+// elements per workgroup of the volume kernel
+template <int P, bool DBL>
+static int prism_vol_elems(bool aa, bool saa) {
+  return !DBL && aa && !saa ? PrismMf<P, true>::EB : PrismLaunch<P, DBL>::EB;
+}
 
 // elements per workgroup of the disu kernel (256 threads)
 constexpr int PRISM_DISU_EB = 8;
@@ -1661,6 +1682,7 @@ static void prism_launch(const TypeArgs& a, const int grid[3], hipStream_t st) {
   const PrismTri<P, R>* tri = (const PrismTri<P, R>*)a.dops;
   const PrismDisuTab<P>* dtab = (const PrismDisuTab<P>*)((const char*)a.dops + prism_disu_offset<P, R>());
   constexpr bool dbl = sizeof(R) == 8;
+  const float* mft = (const float*)((const char*)a.dops + prism_mf_offset<P, R>());
   constexpr int EB = PrismLaunch<P, dbl>::EB, NT = PrismLaunch<P, dbl>::NT;
   constexpr int EBA = PRISM_DISU_EB, NTA = 256, EBC = PrismSurf<P, dbl>::EB, NTC = 256;
   const double eref = a.gas->pref / (a.gas->gamma - 1.0), rho0 = a.gas->rho_ref;
@@ -1670,9 +1692,14 @@ static void prism_launch(const TypeArgs& a, const int grid[3], hipStream_t st) {
   // curved prisms (single meshes only; flux anti-aliasing, general metric)
   if constexpr (!BT) {
     if (a.warp) {
-      if ((a.stage & 2) && grid[K_VOLUME] > 0)
-        hipLaunchKernelGGL((prism_volume<P, R, EB, NT, false, true, false, true>), dim3(grid[K_VOLUME]), dim3(NT), 0,
-                           st, a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, g, eref, rho0);
+      if ((a.stage & 2) && grid[K_VOLUME] > 0) {
+        if constexpr (dbl)
+          hipLaunchKernelGGL((prism_volume<P, R, EB, NT, false, true, false, true>), dim3(grid[K_VOLUME]), dim3(NT), 0,
+                             st, a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, g, eref, rho0);
+        else
+          hipLaunchKernelGGL((prism_volume_mf<P, false, true>), dim3(grid[K_VOLUME]), dim3(PrismMf<P, false>::NT), 0,
+                             st, a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, mft, g, eref, rho0);
+      }
       if ((a.stage & 4) && grid[K_SURFACE] > 0)
         hipLaunchKernelGGL((prism_surface<P, R, EBC, NTC, false, false, true>), dim3(grid[K_SURFACE]), dim3(NTC), 0,
                            st, a.one, a.bt[K_SURFACE], a.segs, a.rk, op, tri, g);
@@ -1685,10 +1712,14 @@ static void prism_launch(const TypeArgs& a, const int grid[3], hipStream_t st) {
     if (a.saa)
       hipLaunchKernelGGL((prism_volume<P, R, EB, NT, BT, true, true, false>), dim3(grid[K_VOLUME]), dim3(NT), 0, st, a.one,
                          a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, g, eref, rho0);
-    else if (a.aa)
-      hipLaunchKernelGGL((prism_volume<P, R, EB, NT, BT, true, false, false>), dim3(grid[K_VOLUME]), dim3(NT), 0, st, a.one,
-                         a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, g, eref, rho0);
-    else
+    else if (a.aa) {
+      if constexpr (dbl)
+        hipLaunchKernelGGL((prism_volume<P, R, EB, NT, BT, true, false, false>), dim3(grid[K_VOLUME]), dim3(NT), 0, st,
+                           a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, g, eref, rho0);
+      else
+        hipLaunchKernelGGL((prism_volume_mf<P, BT, false>), dim3(grid[K_VOLUME]), dim3(PrismMf<P, true>::NT), 0, st,
+                           a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, mft, g, eref, rho0);
+    } else
       hipLaunchKernelGGL((prism_volume<P, R, EB, NT, BT, false, false, false>), dim3(grid[K_VOLUME]), dim3(NT), 0, st,
                          a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, g, eref, rho0);
   }
@@ -1705,7 +1736,7 @@ static void prism_launch(const TypeArgs& a, const int grid[3], hipStream_t st) {
 template <int P, typename R>
 static hipError_t prism_rhs_t(const TypeArgs& a, hipStream_t st) {
   constexpr bool dbl = sizeof(R) == 8;
-  const int ebs[3] = {PRISM_DISU_EB, PrismLaunch<P, dbl>::EB,
+  const int ebs[3] = {PRISM_DISU_EB, prism_vol_elems<P, dbl>(a.aa, a.saa),
                       a.saa ? PrismSurf<P, dbl, true>::EB : PrismSurf<P, dbl>::EB};
   const bool bt = a.bt[0] && a.bt[1] && a.bt[2] && a.segs;
   int grid[3];
@@ -1723,7 +1754,7 @@ static int prism_surf_elems(bool d, bool saa) {
            : (saa ? PrismSurf<P, false, true>::EB : PrismSurf<P, false>::EB);
 }
 
-int prism_block_elems(int p, int prec, int k, bool saa) {
+int prism_block_elems(int p, int prec, int k, bool aa, bool saa) {
   if (k == K_DISU) return PRISM_DISU_EB;
   const bool d = prec == 0;
   if (k == K_SURFACE) {
@@ -1736,10 +1767,10 @@ int prism_block_elems(int p, int prec, int k, bool saa) {
     return 0;
   }
   switch (p) {
-    case 1: return d ? PrismLaunch<1, true>::EB : PrismLaunch<1, false>::EB;
-    case 2: return d ? PrismLaunch<2, true>::EB : PrismLaunch<2, false>::EB;
-    case 3: return d ? PrismLaunch<3, true>::EB : PrismLaunch<3, false>::EB;
-    case 4: return d ? PrismLaunch<4, true>::EB : PrismLaunch<4, false>::EB;
+    case 1: return d ? prism_vol_elems<1, true>(aa, saa) : prism_vol_elems<1, false>(aa, saa);
+    case 2: return d ? prism_vol_elems<2, true>(aa, saa) : prism_vol_elems<2, false>(aa, saa);
+    case 3: return d ? prism_vol_elems<3, true>(aa, saa) : prism_vol_elems<3, false>(aa, saa);
+    case 4: return d ? prism_vol_elems<4, true>(aa, saa) : prism_vol_elems<4, false>(aa, saa);
   }
   return 0;
 }
