@@ -9,8 +9,9 @@
 //   2  triangle planes (variable, plane): face values at the edge points,
 //      jumps, corrected (xi, eta) derivatives, J^-T        [matrix cores]
 //   3  triangle planes (field, plane): the 20 fields at the edge points
-//      (EF) for the face viscous flux                      [matrix cores]
-//   4  normal viscous flux at the own flux points
+//      [matrix cores]; normal viscous flux at the triangle nodes; the edge
+//      fields EF to LDS over the state
+//   4  normal viscous flux at the quadrilateral-face points
 //   5  triangle planes: T_q to the triangle quadrature points, T1 over the
 //      state and gradients                                 [matrix cores]
 //   6  quadrature columns, two half-wave lanes per column (lane and
@@ -18,12 +19,15 @@
 //      interpolation, flux, zeta projection                [matrix cores]
 //   7  triangle planes (variable, plane): projection-divergence [matrix cores]
 // The operators come from L2 as packed chunks, a register per 16 chunks, so
-// no table sits in LDS: at p = 4 an element needs 12 KB and two 5-element
-// workgroups of four waves share a CU, where the form with the tables in LDS
-// ran seven one-wave workgroups at half-filled waves.  Measured (volume
-// group, MI355X): 48^3 cells p = 3 1474 -> 817 us, 262 144 prisms p = 4
-// 5586 -> 2133 us, 32 768 curved prisms p = 3 251 -> 155 us, against the
-// vector kernel with its operator tables in LDS.
+// no table sits in LDS, and every LDS array lies over the dead one before it:
+// 26 KB per four elements at p = 3 (six two-wave workgroups per CU) and 52 KB
+// per five at p = 4 (three four-wave ones), three waves per SIMD at both.
+// Bound by instruction issue: vector and matrix pipes together busy 77% (p = 3)
+// and 70% (p = 4) of the time.  Measured (volume group, MI355X): 48^3 cells
+// p = 3 1474 -> 750 us, 262 144 prisms p = 4 5586 -> 1795 us, 32 768 curved
+// prisms p = 3 251 -> 141 us, against the vector kernel with its operator
+// tables in LDS (8 and 7 waves per CU); with EF and the face records in LDS of
+// their own (five and two workgroups per CU) 817, 2133 and 155 us.
 namespace fr {
 
 template <int P, bool LIN>
@@ -34,12 +38,23 @@ struct PrismMf {
   static constexpr int EB = P == 1 ? 8 : (P == 2 ? 7 : (P == 3 ? 4 : 5));
   static constexpr int W = P == 1 ? 1 : (P == 4 ? 4 : 2), NT = 64 * W;
   static_assert(EB * NTQ <= 32 * W, "two lanes per quadrature column");
-  // T1 rows on 16-byte boundaries (four outputs of a lane in one store),
-  // strides that spread eight lanes' stores over all banks
-  static constexpr int TQ4 = P == 1 ? 4 : (P == 2 ? 12 : (P == 3 ? 20 : 28));
-  static constexpr int SZ_T1 = 20 * n * TQ4;
-  static constexpr int PE0 = C::SZ_A + C::SZ_JE > SZ_T1 ? C::SZ_A + C::SZ_JE : SZ_T1;
-  static constexpr int PE = ((PE0 > C::SZ_Z ? PE0 : C::SZ_Z) + 3) / 4 * 4;
+  // LDS per element, every array from offset 0 over the dead one before it:
+  // state, gradients and neighbour states with the face records behind them
+  // (FRO) | the fields at the edge points EF | T1 | Z.  T1 rows of TQS: on
+  // 16-byte boundaries (p <= 3: four outputs of a lane in one store, strides
+  // that spread eight lanes' stores over all banks), 8-byte ones at p = 4,
+  // where the longer rows would cost a workgroup per CU
+  static constexpr int TQS = P == 1 ? 4 : (P == 2 ? 12 : (P == 3 ? 20 : 26));
+  static constexpr int SZ_T1 = 20 * n * TQS;
+  // Z variables ZVS apart, so that the lanes of a plane sweep (4 variables, n
+  // planes) read different banks
+  static constexpr int ZVS = P == 4 ? NTQ * n + 8 : C::ZVS, SZ_Z = 3 * NVF * ZVS;
+  static constexpr int mx(int a, int b) { return a > b ? a : b; }
+  static constexpr int FRO = (mx(C::SZ_A + C::SZ_J, C::SZ_EF) + 3) / 4 * 4;  // records, geometry, permutations
+  static constexpr int SZ_F = FRO + 40 + (MAX_PERMS * NFP + 3) / 4;
+  static constexpr int PE0 = (mx(SZ_F, mx(SZ_T1, SZ_Z)) + 3) / 4 * 4;
+  // p = 3: elements 16 banks apart (a wave's 32 columns lie in two elements)
+  static constexpr int PE = P == 3 ? PE0 + 16 : PE0;
   // zeta levels: the lower half wave takes the first L0, the upper the rest
   static constexpr int L0 = (m + 1) / 2;
   static_assert(L0 <= 4 && m - L0 >= 1, "one row tile of levels");
@@ -109,7 +124,7 @@ static void prism_mf_pack(const RefElem& r, float* o) {
 }
 
 template <int P, bool BT, bool WARP>
-__global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu_waves_per_eu(3)))
     prism_volume_mf(const Seg one, const BlkRef* __restrict__ bt, const Seg* __restrict__ segs, const bool from_ust,
                     const PrismOps<P, float> op, const PrismTri<P, float>* __restrict__ tri,
                     const float* __restrict__ tab, const Gas<float> g, const double eref, const double rho0) {
@@ -123,9 +138,6 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
   constexpr int NVF = C::NVF, V0 = C::V0, EB = M::EB, W = M::W, NT_ = M::NT, PE = M::PE;
   __shared__ __attribute__((aligned(16))) R smem[EB * PE];
   __shared__ R sMet[EB][10];
-  __shared__ FaceRec sFR[EB * 5];
-  __shared__ R sFG[EB * 5][4];
-  __shared__ uint8_t sPerm[MAX_PERMS * NFP];
   __shared__ R sV[WARP ? EB : 1][18];  // curved: element vertices
   int e0;
   const Seg sg = seg_of<BT>(one, bt, segs, EB, e0);
@@ -140,18 +152,22 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
   const int E = sg.E, slot_base = sg.slot_base, tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #define XS(le) (smem + (le)*PE)           /* [20][NU]                            */
-#define JS(le) (smem + (le)*PE + C::SZ_A) /* [5][5][NFP] neighbour u^f; later EF */
-#define TS(le) (smem + (le)*PE)           /* [20][n][TQ4]                        */
+#define JS(le) (smem + (le)*PE + C::SZ_A) /* [5][5][NFP] neighbour u^f           */
+#define ES(le) (smem + (le)*PE)           /* [20][EFS] fields at the edge points */
+#define TS(le) (smem + (le)*PE)           /* [20][n][TQS]                        */
 #define ZS(le) (smem + (le)*PE)           /* [3][NVF][ZVS]                       */
+#define FR(le) (reinterpret_cast<FaceRec*>(smem + (le)*PE + M::FRO))       /* [5]    */
+#define FG(le) (reinterpret_cast<R(*)[4]>(smem + (le)*PE + M::FRO + 20))   /* [5][4] */
+  uint8_t* sPerm = reinterpret_cast<uint8_t*>(smem + M::FRO + 40);         // behind element 0's records
 
   // phase 0: face records, face geometry and permutations first, so the
   // neighbour gather is one global load per value; out-of-range items load
   // from a valid address and never reach an output
   for (int it = tid; it < EB * 5; it += NT_) {
     const int slot = slot_base + (e0 + it / 5 < E ? e0 * 5 + it : 0);
-    sFR[it] = faces[slot];
+    FR(it / 5)[it % 5] = faces[slot];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) sFG[it][k] = fgeo[4 * slot + k];
+    for (int k = 0; k < 4; ++k) FG(it / 5)[it % 5][k] = fgeo[4 * slot + k];
   }
   for (int it = tid; it < sg.nperm * NFP; it += NT_) sPerm[it] = perms[it];
   if constexpr (WARP) {
@@ -189,7 +205,7 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
     const int le = itc / F::PPE;
     int f, r;
     face_point(itc - le * F::PPE, f, r);
-    const FaceRec fr = sFR[le * 5 + f];
+    const FaceRec fr = FR(le)[f];
     const R* __restrict__ src = Uf + (size_t)fr.npo * 5 + sPerm[(fr.info >> 1) * NFP + r];
     const int fs = F::fsz(f);
 #pragma unroll
@@ -233,8 +249,8 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
       xm += op.lb[k] * x[k];
       xp += op.rb[k] * x[k];
     }
-    const R wm = (sFR[le * 5].info & 1) ? R(0.5) + g.beta : R(0.5) - g.beta;
-    const R wp = (sFR[le * 5 + 1].info & 1) ? R(0.5) + g.beta : R(0.5) - g.beta;
+    const R wm = (FR(le)[0].info & 1) ? R(0.5) + g.beta : R(0.5) - g.beta;
+    const R wp = (FR(le)[1].info & 1) ? R(0.5) + g.beta : R(0.5) - g.beta;
     const R jm = wm * (JS(le)[(0 * 5 + v) * NFP + t] - xm), jp = wp * (JS(le)[(1 * 5 + v) * NFP + t] - xp);
 #pragma unroll
     for (int k = 0; k < n; ++k) {
@@ -277,7 +293,7 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
       for (int t = 0; t < NTN; ++t) og.col(t, x[t], gr);
 #pragma unroll
       for (int q = 0; q < 3 * n; ++q) {
-        const R w = (sFR[le * 5 + 2 + q / n].info & 1) ? R(0.5) + g.beta : R(0.5) - g.beta;
+        const R w = (FR(le)[2 + q / n].info & 1) ? R(0.5) + g.beta : R(0.5) - g.beta;
         og.col(NTN + q, w * (jq[q] - fe[q / 4][q % 4]), gr);
       }
       if (it < NI) {
@@ -316,11 +332,13 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
     lds_barrier();
   }
 
-  // phase 3: the 20 fields at the quadrilateral-face points (gradcoru_fpts)
-  // into EF, over the neighbour values.  The plane values stay in registers
-  // for phase 5.
+  // phase 3: triangle planes of the 20 fields, in registers until phase 5;
+  // their values at the edge points (gradcoru_fpts), in registers until EF
+  // may overwrite the state; the normal viscous flux at the triangle nodes
+  // (both faces of a line)
   constexpr int NP = EB * 20 * n, NIT = (NP + NT_ - 1) / NT_;
   R xv[NIT][NTN];
+  mf4v fe[NIT][M::TE];
 #pragma unroll
   for (int j = 0; j < NIT; ++j) {
     const int it = tid + j * NT_, itc = it < NP ? it : 0;
@@ -328,108 +346,109 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
     const R* x = XS(le) + fld * NU + NTN * k;
 #pragma unroll
     for (int t = 0; t < NTN; ++t) xv[j][t] = x[t];
-    mf4v fe[M::TE];
 #pragma unroll
-    for (int t = 0; t < M::TE; ++t) fe[t] = mf4v{0, 0, 0, 0};
+    for (int t = 0; t < M::TE; ++t) fe[j][t] = mf4v{0, 0, 0, 0};
 #pragma unroll
-    for (int t = 0; t < NTN; ++t) oe.col(t, xv[j][t], fe);
+    for (int t = 0; t < NTN; ++t) oe.col(t, xv[j][t], fe[j]);
+  }
+  // (from the first thread on; phase 4 goes from the last, so that the waves share the surplus)
+  for (int it = tid; it < EB * NTN; it += NT_) {
+    const int le = it / NTN, t = it - le * NTN, e = e0 + le;
+    if (e >= E) continue;
+    const R* X = XS(le) + t;
+    R fm[20], fp[20];
+#pragma unroll
+    for (int fld = 0; fld < 20; ++fld) {
+      R sm = R(0), sp = R(0);
+#pragma unroll
+      for (int k = 0; k < n; ++k) {
+        const R x = X[fld * NU + NTN * k];
+        sm += op.lb[k] * x;
+        sp += op.rb[k] * x;
+      }
+      fm[fld] = sm;
+      fp[fld] = sp;
+    }
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      const R* w = side ? fp : fm;
+      const int po = sg.po_base + e * F::PPE + side * NTN;
+      R nn[3];
+      if constexpr (WARP) {
+        // own outward unit normal: +-S_zeta / |S_zeta| at the triangle node
+        R S[3][3], det;
+        wedge_metric(&sV[le][0], tri->nodes[t][0], tri->nodes[t][1], side ? R(1) : R(-1), S, det);
+        const R im = rcp(sqrt(S[2][0] * S[2][0] + S[2][1] * S[2][1] + S[2][2] * S[2][2]));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) nn[c] = (side ? im : -im) * S[2][c];
+      } else {
+        const R sgn = (FR(le)[side].info & 1) ? R(1) : R(-1);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) nn[c] = sgn * FG(le)[side][c];
+      }
+      R u[5], q[3][5], V[4];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        u[v] = w[v];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) q[d][v] = w[5 + d * 5 + v];
+      }
+      normal_viscous(u, q, nn, g, V);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) Vf[(size_t)po * 4 + kk * NTN + t] = V[kk];
+    }
+  }
+  lds_barrier();
+#pragma unroll
+  for (int j = 0; j < NIT; ++j) {
+    const int it = tid + j * NT_;
     if (it < NP) {
-      R* EF = JS(le) + fld * C::EFS + n * k;
+      const int le = it / (20 * n), fk = it - le * (20 * n), fld = fk / n, k = fk - fld * n;
+      R* EF = ES(le) + fld * C::EFS + n * k;
 #pragma unroll
-      for (int q = 0; q < 3 * n; ++q) EF[(q / n) * NFP + q % n] = fe[q / 4][q % 4];
+      for (int q = 0; q < 3 * n; ++q) EF[(q / n) * NFP + q % n] = fe[j][q / 4][q % 4];
     }
   }
   lds_barrier();
 
-  // phase 4: normal viscous flux at the own flux points, whole waves of
-  // quadrilateral-face points first, then of triangle nodes (both faces)
-  constexpr int NQP = EB * 3 * NFP, WQ = (NQP + 63) / 64, NTP = EB * NTN, WT = (NTP + 63) / 64;
-  for (int wp = wave; wp < WQ + WT; wp += W) {
-    if (wp < WQ) {
-      const int it = wp * 64 + lane;
-      const int le = it / (3 * NFP), r1 = it - le * (3 * NFP), e = e0 + le;
-      if (it >= NQP || e >= E) continue;
-      const int ed = r1 / NFP, r2 = r1 - ed * NFP;
-      const int lf = le * 5 + 2 + ed, po = sg.po_base + e * F::PPE + F::foff(2 + ed);
-      R nn[3];
-      if constexpr (WARP) {
-        // own outward unit normal: (nx S_xi + ny S_eta) normalised at the edge point
-        const int k = r2 / n, i = r2 - k * n;
-        R xi, eta, nx, ny, S[3][3], det;
-        edge_point(ed, psel(op.x, i), xi, eta);
-        edge_normal<R>(ed, nx, ny);
-        wedge_metric(&sV[le][0], xi, eta, psel(op.x, k), S, det);
-        R vv[3];
+  // phase 4: normal viscous flux at the quadrilateral-face points
+  for (int it = NT_ - 1 - tid; it < EB * 3 * NFP; it += NT_) {
+    const int le = it / (3 * NFP), r1 = it - le * (3 * NFP), e = e0 + le;
+    if (e >= E) continue;
+    const int ed = r1 / NFP, r2 = r1 - ed * NFP;
+    const int po = sg.po_base + e * F::PPE + F::foff(2 + ed);
+    R nn[3];
+    if constexpr (WARP) {
+      // own outward unit normal: (nx S_xi + ny S_eta) normalised at the edge point
+      const int k = r2 / n, i = r2 - k * n;
+      R xi, eta, nx, ny, S[3][3], det;
+      edge_point(ed, psel(op.x, i), xi, eta);
+      edge_normal<R>(ed, nx, ny);
+      wedge_metric(&sV[le][0], xi, eta, psel(op.x, k), S, det);
+      R vv[3];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) vv[c] = nx * S[0][c] + ny * S[1][c];
-        const R im = rcp(sqrt(vv[0] * vv[0] + vv[1] * vv[1] + vv[2] * vv[2]));
+      for (int c = 0; c < 3; ++c) vv[c] = nx * S[0][c] + ny * S[1][c];
+      const R im = rcp(sqrt(vv[0] * vv[0] + vv[1] * vv[1] + vv[2] * vv[2]));
 #pragma unroll
-        for (int c = 0; c < 3; ++c) nn[c] = im * vv[c];
-      } else {
-        const R sgn = (sFR[lf].info & 1) ? R(1) : R(-1);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) nn[c] = sgn * sFG[lf][c];
-      }
-      const R* EF = JS(le) + r1;
-      R u[5], q[3][5], V[4];
-#pragma unroll
-      for (int fld = 0; fld < 20; ++fld) {
-        const R s = EF[fld * C::EFS];
-        if (fld < 5)
-          u[fld] = s;
-        else
-          q[(fld - 5) / 5][(fld - 5) % 5] = s;
-      }
-      normal_viscous(u, q, nn, g, V);
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) Vf[(size_t)po * 4 + kk * NFP + r2] = V[kk];
+      for (int c = 0; c < 3; ++c) nn[c] = im * vv[c];
     } else {
-      const int it = (wp - WQ) * 64 + lane;
-      const int le = it / NTN, t = it - le * NTN, e = e0 + le;
-      if (it >= NTP || e >= E) continue;
-      const R* X = XS(le) + t;
-      R fm[20], fp[20];
+      const R sgn = (FR(le)[2 + ed].info & 1) ? R(1) : R(-1);
 #pragma unroll
-      for (int fld = 0; fld < 20; ++fld) {
-        R sm = R(0), sp = R(0);
-#pragma unroll
-        for (int k = 0; k < n; ++k) {
-          const R x = X[fld * NU + NTN * k];
-          sm += op.lb[k] * x;
-          sp += op.rb[k] * x;
-        }
-        fm[fld] = sm;
-        fp[fld] = sp;
-      }
-#pragma unroll
-      for (int side = 0; side < 2; ++side) {
-        const R* w = side ? fp : fm;
-        const int lf = le * 5 + side, po = sg.po_base + e * F::PPE + side * NTN;
-        R nn[3];
-        if constexpr (WARP) {
-          // own outward unit normal: +-S_zeta / |S_zeta| at the triangle node
-          R S[3][3], det;
-          wedge_metric(&sV[le][0], tri->nodes[t][0], tri->nodes[t][1], side ? R(1) : R(-1), S, det);
-          const R im = rcp(sqrt(S[2][0] * S[2][0] + S[2][1] * S[2][1] + S[2][2] * S[2][2]));
-#pragma unroll
-          for (int c = 0; c < 3; ++c) nn[c] = (side ? im : -im) * S[2][c];
-        } else {
-          const R sgn = (sFR[lf].info & 1) ? R(1) : R(-1);
-#pragma unroll
-          for (int c = 0; c < 3; ++c) nn[c] = sgn * sFG[lf][c];
-        }
-        R u[5], q[3][5], V[4];
-#pragma unroll
-        for (int v = 0; v < 5; ++v) {
-          u[v] = w[v];
-#pragma unroll
-          for (int d = 0; d < 3; ++d) q[d][v] = w[5 + d * 5 + v];
-        }
-        normal_viscous(u, q, nn, g, V);
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) Vf[(size_t)po * 4 + kk * NTN + t] = V[kk];
-      }
+      for (int c = 0; c < 3; ++c) nn[c] = sgn * FG(le)[2 + ed][c];
     }
+    const R* EF = ES(le) + r1;
+    R u[5], q[3][5], V[4];
+#pragma unroll
+    for (int fld = 0; fld < 20; ++fld) {
+      const R s = EF[fld * C::EFS];
+      if (fld < 5)
+        u[fld] = s;
+      else
+        q[(fld - 5) / 5][(fld - 5) % 5] = s;
+    }
+    normal_viscous(u, q, nn, g, V);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) Vf[(size_t)po * 4 + kk * NFP + r2] = V[kk];
   }
   Mf4Op<M::TT, NTN> ot;
   ot.load(tab + B::tq, lane);
@@ -448,9 +467,16 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
 #pragma unroll
     for (int t = 0; t < NTN; ++t) ot.col(t, xv[j][t], s);
     if (it < NP) {
-      mf4v* T = reinterpret_cast<mf4v*>(TS(le) + fk * M::TQ4);
+      R* T = TS(le) + fk * M::TQS;
+      if constexpr (M::TQS % 4 == 0) {
 #pragma unroll
-      for (int t = 0; t < M::TT; ++t) T[t] = s[t];
+        for (int t = 0; t < M::TT; ++t) reinterpret_cast<mf4v*>(T)[t] = s[t];
+      } else {
+        typedef float f2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int t = 0; t < NTQ / 2 + NTQ % 2; ++t)
+          reinterpret_cast<f2*>(T)[t] = f2{s[t / 2][2 * (t % 2)], s[t / 2][2 * (t % 2) + 1]};
+      }
     }
   }
   lds_barrier();
@@ -473,7 +499,7 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
     for (int fld = 0; fld < 20; ++fld) {
       w[fld] = mf4v{0, 0, 0, 0};
 #pragma unroll
-      for (int k = 0; k < n; ++k) w[fld] = mf4<3>(azi, T[(fld * n + k) * M::TQ4], w[fld], k);
+      for (int k = 0; k < n; ++k) w[fld] = mf4<3>(azi, T[(fld * n + k) * M::TQS], w[fld], k);
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d)
@@ -544,7 +570,7 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
     for (int i = 0; i < NV; i += 2) {
       const bool two = i + 1 < NV;
       const R s = half_sums(val(i), val(two ? i + 1 : i));
-      const int z0 = (i / n) * C::ZVS + i % n, z1 = two ? ((i + 1) / n) * C::ZVS + (i + 1) % n : z0;
+      const int z0 = (i / n) * M::ZVS + i % n, z1 = two ? ((i + 1) / n) * M::ZVS + (i + 1) % n : z0;
       if (col && (two || !half)) Z[half ? z1 : z0] = s;
     }
   }
@@ -565,14 +591,14 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
 #pragma unroll
       for (int t = 0; t < 4 * M::TPG; ++t) lin[t] = out[t0 + t < NTN ? t0 + t : 0];
     }
-    const R* Z = ZS(le) + vv * C::ZVS + k;
+    const R* Z = ZS(le) + vv * M::ZVS + k;
     mf4v s[M::TPG];
 #pragma unroll
     for (int t = 0; t < M::TPG; ++t) s[t] = mf4v{0, 0, 0, 0};
 #pragma unroll
     for (int tq = 0; tq < NTQ; ++tq)
 #pragma unroll
-      for (int d = 0; d < 3; ++d) opj.col(3 * tq + d, Z[d * NVF * C::ZVS + tq * n], s);
+      for (int d = 0; d < 3; ++d) opj.col(3 * tq + d, Z[d * NVF * M::ZVS + tq * n], s);
     if (ok) {
 #pragma unroll
       for (int t = 0; t < 4 * M::TPG; ++t) {
@@ -584,6 +610,9 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
   }
 #undef XS
 #undef JS
+#undef ES
+#undef FR
+#undef FG
 #undef TS
 #undef ZS
 }
