@@ -566,6 +566,12 @@ __global__ void __launch_bounds__(NT) dense_volume(const Seg sg, const bool from
 // element's columns in LDS.  Products that feed point-wise physics (face and
 // quadrature values) go through LDS rows; the three directions of the
 // projection-divergence are one product with K concatenated.
+// Bound by instruction issue (single-precision matrix and vector instructions
+// share the ALUs; together busy 83% of the time at tetrahedra p = 3), half of
+// it index arithmetic: with the tile loops on the scalar unit, one flux point
+// per gather item and the constant fluxes formed once in an idle wave,
+// 196 608 tetrahedra p = 3 take 746 us instead of 814, 41 472 pyramids 238
+// instead of 251.
 typedef float mf4 __attribute__((ext_vector_type(4)));
 typedef double md4 __attribute__((ext_vector_type(4)));
 template <typename R>
@@ -651,6 +657,13 @@ __device__ __forceinline__ void wave_tiles(int T, int NW, int wave, int& t0, int
   t1 = (wave + 1) * T / NW;
 }
 
+// j / D for the small column numbers of a workgroup (j < 4096, D <= 20), in
+// one 24-bit multiplication
+template <int D>
+__device__ __forceinline__ int div_small(int j) {
+  return (int)(__umul24((unsigned)j, (65536u + D - 1) / D) >> 16);
+}
+
 template <int ET, int P, typename R, int EB, int NT, bool AA>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<ET, P, R, AA>::min_waves)))
     dense_volume_mf(const Seg sg, const bool from_ust, const R* __restrict__ ops, const Gas<R> g,
@@ -697,7 +710,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
 #define FRQ(le, f) (RIN ? ((FaceRec*)(smem + (le)*PE + ROFF))[f] : sFRA[(le)*NFACE + (f)])
 #define FGQ(le, f, k) (RIN ? (smem + (le)*PE + ROFF + NFACE * 16 / (int)sizeof(R))[4 * (f) + (k)] \
                            : sFGA[((le)*NFACE + (f)) * 4 + (k)])
-  const int e0 = blockIdx.x * EB, E = sg.E, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int e0 = blockIdx.x * EB, E = sg.E, tid = threadIdx.x, lane = tid & 63;
+  // wave-uniform, so that the tile loops run on the scalar unit
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const double* __restrict__ U = from_ust ? sg.ust : sg.U;
   const R* __restrict__ Uf = (const R*)sg.Uf;
   R* __restrict__ Vf = (R*)sg.Vf;
@@ -755,7 +770,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
   // thread's loads are in flight together; out-of-range items read valid
   // addresses and are not stored.
   const int nv = E - e0 < EB ? E - e0 : EB;  // valid elements of the workgroup
-  constexpr int NSL = (EB * 5 * NU + NT - 1) / NT, NGL = (EB * 5 * NF + NT - 1) / NT;
+  constexpr int NSL = (EB * 5 * NU + NT - 1) / NT, NGL = (EB * NF + NT - 1) / NT;
   double xs[NSL];
   float xb[FC ? NSL : 1];
 #pragma unroll
@@ -781,21 +796,28 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
       sMetA[le][k] = met[e0 + le < E ? (size_t)(e0 + le) * 10 + k : 0];
     }
   lds_barrier();
-  R gx[NGL];
-  float gn[FC ? NGL : 1], go[FC ? NGL : 1];
+  // one flux point per item with its five fields
+  R gx[NGL][5];
+  float gn[FC ? NGL : 1][5], go[FC ? NGL : 1][5];
 #pragma unroll
   for (int k = 0; k < NGL; ++k) {
     const int it = tid + k * NT;
-    const int itc = it < EB * 5 * NF ? it : 0;
-    const int le = itc / (5 * NF), r0 = itc - le * (5 * NF), v = r0 / NF, fp = r0 - v * NF;
+    const int itc = it < EB * NF ? it : 0;
+    const int le = itc / NF, fp = itc - le * NF;
     const int f = C::face_of(fp), t = C::point_of(fp);
     const FaceRec fr = FRQ(le, f);
-    gx[k] = Uf[(size_t)fr.npo * 5 + v * C::fsz(f) + sPerm[(fr.info >> 1) * NFPS + t]];
+    const R* __restrict__ src = Uf + (size_t)fr.npo * 5 + sPerm[(fr.info >> 1) * NFPS + t];
+    const int fs = C::fsz(f);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) gx[k][v] = src[v * fs];
     if constexpr (FC) {
       // neighbour value relative to this element's base state
       const int e = le < nv ? e0 + le : e0;
-      gn[k] = sg.Ub[(size_t)fr.nbr * 5 + v];
-      go[k] = sg.Ub[(size_t)(sg.slot_base + e * NFACE) * 5 + v];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        gn[k][v] = sg.Ub[(size_t)fr.nbr * 5 + v];
+        go[k][v] = sg.Ub[(size_t)(sg.slot_base + e * NFACE) * 5 + v];
+      }
     }
   }
 #pragma unroll
@@ -816,26 +838,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
 #pragma unroll
   for (int k = 0; k < NGL; ++k) {
     const int it = tid + k * NT;
-    if (it < EB * 5 * NF) {
-      const int le = it / (5 * NF), r0 = it - le * (5 * NF);
-      U2(le)[r0] = FC ? gx[k] + (gn[k] - go[k]) : gx[k];
-    }
-  }
-  if (FC && tid < EB) {
-    const int e = e0 + tid < E ? e0 + tid : 0;
-    if constexpr (LEAN) {
-      R fc[12];
-      const_flux(sg.Ub + (size_t)(sg.slot_base + e * NFACE) * 5, met + (size_t)e * 10, g, fc);
-      if (e0 + tid < E)
+    if (it < EB * NF) {
+      const int le = it / NF, fp = it - le * NF;
 #pragma unroll
-        for (int k = 0; k < 12; ++k) sg.fbar[(size_t)e * 12 + k] = fc[k];
-    } else {
-      const_flux(sg.Ub + (size_t)(sg.slot_base + e * NFACE) * 5, &sMetA[tid][0], g, &sFcA[tid][0]);
-#pragma unroll
-      for (int v = 0; v < 5; ++v) sUbA[tid][v] = sg.Ub[(size_t)(sg.slot_base + e * NFACE) * 5 + v];
-      if (e0 + tid < E)
-#pragma unroll
-        for (int k = 0; k < 12; ++k) sg.fbar[(size_t)e * 12 + k] = sFcA[tid][k];
+      for (int v = 0; v < 5; ++v) U2(le)[v * NF + fp] = FC ? gx[k][v] + (gn[k][v] - go[k][v]) : gx[k][v];
     }
   }
   lds_barrier();
@@ -850,7 +856,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
     for (int t = t0; t < t1; ++t) {
       const int mt = t / NTL, nt = t - mt * NTL, j = nt * 16 + (lane & 15);
       const bool ok = j < 5 * EB;
-      const int le = ok ? j / 5 : EB - 1, v = ok ? j % 5 : 0;
+      const int le = ok ? div_small<5>(j) : EB - 1, v = ok ? j - 5 * le : 0;
       if (mt != amt) {
         mf_load<C::KSU>(a, ops + C::O_PM0 + mt * C::KSU * 64, lane);
         amt = mt;
@@ -882,7 +888,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
     for (int t = t0; t < t1; ++t) {
       const int mt = t / NTL, nt = t - mt * NTL, j = nt * 16 + (lane & 15);
       const bool ok = j < 5 * EB;
-      const int le = ok ? j / 5 : EB - 1, v = ok ? j % 5 : 0;
+      const int le = ok ? div_small<5>(j) : EB - 1, v = ok ? j - 5 * le : 0;
       if (mt != amt) {
         const R* Ap = ops + C::O_PG + mt * (C::KSU + C::KSF) * 64;
         mf_load<C::KSU>(au, Ap, lane);
@@ -905,6 +911,24 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
   }
   lds_barrier();
 
+  // single precision: the elements' constant fluxes, one lane per element in
+  // the last wave, which this phase leaves idle (in phase 0 the other waves
+  // waited for it); LEAN keeps them in registers for the quadrature phase
+  const int lc = tid - (NT - EB);
+  R fcr[FC ? 12 : 1];
+  if (FC && lc >= 0) {
+    const int e = e0 + lc < E ? e0 + lc : e0;
+    const_flux(sg.Ub + (size_t)(sg.slot_base + e * NFACE) * 5, met + (size_t)e * 10, g, fcr);
+    if (e0 + lc < E)
+#pragma unroll
+      for (int k = 0; k < 12; ++k) sg.fbar[(size_t)e * 12 + k] = fcr[k];
+    if constexpr (!LEAN) {
+#pragma unroll
+      for (int k = 0; k < 12; ++k) sFcA[lc][k] = fcr[k];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) sUbA[lc][v] = sg.Ub[(size_t)(sg.slot_base + e * NFACE) * 5 + v];
+    }
+  }
   // phase 3: physical gradient q = J^-T q~ (eq. FR-gradcoru), in place
   for (int it = tid; it < EB * NU; it += NT) {
     const int le = it / NU, s = it - le * NU;
@@ -929,7 +953,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
     for (int t = t0; t < t1; ++t) {
       const int mt = t / NTL, nt = t - mt * NTL, j = nt * 16 + (lane & 15);
       const bool ok = j < 20 * EB;
-      const int le = ok ? j / 20 : EB - 1, c = ok ? j % 20 : 0;
+      const int le = ok ? div_small<20>(j) : EB - 1, c = ok ? j - 20 * le : 0;
       if (mt != amt) {
         mf_load<C::KSU>(a, ops + C::O_PM0 + mt * C::KSU * 64, lane);
         amt = mt;
@@ -996,7 +1020,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
     for (int t = wave; t < C::MTU * NTL; t += NW) {
       const int mt = t / NTL, nt = t - mt * NTL, j = nt * 16 + (lane & 15);
       const bool ok = j < NVF * EB;
-      const int le = ok ? j / NVF : EB - 1, v = ok ? V0 + j % NVF : V0;
+      const int le = ok ? div_small<NVF>(j) : EB - 1, v = ok ? V0 + j - NVF * le : V0;
       const R* Ap = ops + C::O_PK0 + mt * 3 * C::KSU * 64;
       V4 acc = {R(0), R(0), R(0), R(0)};
 #pragma unroll
@@ -1027,7 +1051,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
     for (int t = t0; t < t1; ++t) {
       const int mt = t / NTL, nt = t - mt * NTL, j = nt * 16 + (lane & 15);
       const bool ok = j < 20 * EB;
-      const int le = ok ? j / 20 : EB - 1, c = ok ? j % 20 : 0;
+      const int le = ok ? div_small<20>(j) : EB - 1, c = ok ? j - 20 * le : 0;
       if (mt != amt) {
         mf_load<C::KSU>(a, ops + C::O_PM7 + mt * C::KSU * 64, lane);
         amt = mt;
@@ -1046,15 +1070,16 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
   if constexpr (LEAN) {
     // the state region is dead now: element le's metrics, base state and
     // constant flux go to XS(le) + [0, 27) for the flux of every point
-    if (tid < EB) {
-      R* x = XS(tid);
-      const size_t e = ec(tid);
+    if (lc >= 0) {
+      R* x = XS(lc);
+      const size_t e = ec(lc);
 #pragma unroll
       for (int k = 0; k < 10; ++k) x[k] = met[e * 10 + k];
       if constexpr (FC) {  // single precision: base state and constant flux
 #pragma unroll
         for (int v = 0; v < 5; ++v) x[10 + v] = sg.Ub[(size_t)(sg.slot_base + e * NFACE) * 5 + v];
-        const_flux(sg.Ub + (size_t)(sg.slot_base + e * NFACE) * 5, met + e * 10, g, x + 15);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) x[15 + k] = fcr[k];
       }
     }
     lds_barrier();
@@ -1087,7 +1112,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
     for (int t = wave; t < C::MTU * NTL; t += NW) {
       const int mt = t / NTL, nt = t - mt * NTL, j = nt * 16 + (lane & 15);
       const bool ok = j < NVF * EB;
-      const int le = ok ? j / NVF : EB - 1, v = ok ? V0 + j % NVF : V0;
+      const int le = ok ? div_small<NVF>(j) : EB - 1, v = ok ? V0 + j - NVF * le : V0;
       const R* Ap = ops + C::O_PAP + mt * 3 * C::KSQ * 64;
       V4 acc = {R(0), R(0), R(0), R(0)};
 #pragma unroll
