@@ -1523,6 +1523,7 @@ __global__ void __launch_bounds__(NT_)
 }
 
 }  // namespace fr
+#include "prism_volume_d.h"
 #include "prism_volume_mf.h"
 namespace fr {
 
@@ -1598,7 +1599,7 @@ static void pack_disu(const RefElem& r, PrismDisuTab<P>* o) {
     }
 }
 
-// byte offset of the matrix-core table (single precision) behind the disu table
+// byte offset of the volume kernel's packed operators behind the disu table
 template <int P, typename R>
 constexpr size_t prism_mf_offset() {
   return (prism_disu_offset<P, R>() + sizeof(PrismDisuTab<P>) + 255) / 256 * 256;
@@ -1606,19 +1607,23 @@ constexpr size_t prism_mf_offset() {
 
 template <int P, typename R>
 static size_t prism_bytes_t() {
-  return prism_mf_offset<P, R>() + (sizeof(R) == 4 ? PrismMfTab<P>::size * sizeof(float) : 0);
+  return prism_mf_offset<P, R>() +
+         (sizeof(R) == 4 ? PrismMfTab<P>::size * sizeof(float) : PrismDTab<P>::size * sizeof(double));
 }
 
 template <int P, typename R>
 static void prism_pack_t(const RefElem& r, void* dst) {
   pack_tri<P, R>(r.tri, (PrismTri<P, R>*)dst);
   pack_disu<P>(r, (PrismDisuTab<P>*)((char*)dst + prism_disu_offset<P, R>()));
-  if constexpr (sizeof(R) == 4) prism_mf_pack<P>(r, (float*)((char*)dst + prism_mf_offset<P, R>()));
+  if constexpr (sizeof(R) == 4)
+    prism_mf_pack<P>(r, (float*)((char*)dst + prism_mf_offset<P, R>()));
+  else
+    prism_d_pack<P>(r, (double*)((char*)dst + prism_mf_offset<P, R>()));
 }
 
 // the device table of one order and precision: the prism operators in the
-// working precision, the double-precision disu operators, and in single
-// precision the packed operators of the matrix-core volume kernel
+// working precision, the double-precision disu operators, and the packed
+// operators of the volume kernel with flux anti-aliasing
 size_t prism_ops_bytes(int p, int prec) {
   const bool d = prec == 0;
   switch (p) {
@@ -1640,10 +1645,9 @@ void prism_ops_pack(const RefElem& r, int prec, void* dst) {
   }
 }
 
-// Launch shapes of the vector volume kernel: two threads per quadrature
-// column.  It runs double precision, and in single precision what the
-// matrix-core kernel (PrismMf) does not cover: no flux anti-aliasing, and
-// surface-flux anti-aliasing.
+// Launch shapes of prism_volume: two threads per quadrature column.  It runs
+// what prism_volume_mf (single precision) and prism_volume_d (double) do not
+// cover: no flux anti-aliasing, and surface-flux anti-aliasing.
 template <int P, bool DBL>
 struct PrismLaunch;
 template <> struct PrismLaunch<1, false> { static constexpr int EB = 8, NT = 64; };   // 64 column threads
@@ -1659,7 +1663,8 @@ template <> struct PrismLaunch<4, true> { static constexpr int EB = 1, NT = 64; 
 // elements per workgroup of the volume kernel
 template <int P, bool DBL>
 static int prism_vol_elems(bool aa, bool saa) {
-  return !DBL && aa && !saa ? PrismMf<P, true>::EB : PrismLaunch<P, DBL>::EB;
+  if (!aa || saa) return PrismLaunch<P, DBL>::EB;
+  return DBL ? PrismD<P, true>::EB : PrismMf<P, true>::EB;
 }
 
 // elements per workgroup of the disu kernel (256 threads)
@@ -1682,7 +1687,7 @@ static void prism_launch(const TypeArgs& a, const int grid[3], hipStream_t st) {
   const PrismTri<P, R>* tri = (const PrismTri<P, R>*)a.dops;
   const PrismDisuTab<P>* dtab = (const PrismDisuTab<P>*)((const char*)a.dops + prism_disu_offset<P, R>());
   constexpr bool dbl = sizeof(R) == 8;
-  const float* mft = (const float*)((const char*)a.dops + prism_mf_offset<P, R>());
+  const R* mft = (const R*)((const char*)a.dops + prism_mf_offset<P, R>());
   constexpr int EB = PrismLaunch<P, dbl>::EB, NT = PrismLaunch<P, dbl>::NT;
   constexpr int EBA = PRISM_DISU_EB, NTA = 256, EBC = PrismSurf<P, dbl>::EB, NTC = 256;
   const double eref = a.gas->pref / (a.gas->gamma - 1.0), rho0 = a.gas->rho_ref;
@@ -1694,8 +1699,8 @@ static void prism_launch(const TypeArgs& a, const int grid[3], hipStream_t st) {
     if (a.warp) {
       if ((a.stage & 2) && grid[K_VOLUME] > 0) {
         if constexpr (dbl)
-          hipLaunchKernelGGL((prism_volume<P, R, EB, NT, false, true, false, true>), dim3(grid[K_VOLUME]), dim3(NT), 0,
-                             st, a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, g, eref, rho0);
+          hipLaunchKernelGGL((prism_volume_d<P, false, true>), dim3(grid[K_VOLUME]), dim3(PrismD<P, false>::NT), 0,
+                             st, a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, mft, g, eref, rho0);
         else
           hipLaunchKernelGGL((prism_volume_mf<P, false, true>), dim3(grid[K_VOLUME]), dim3(PrismMf<P, false>::NT), 0,
                              st, a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, mft, g, eref, rho0);
@@ -1714,8 +1719,8 @@ static void prism_launch(const TypeArgs& a, const int grid[3], hipStream_t st) {
                          a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, g, eref, rho0);
     else if (a.aa) {
       if constexpr (dbl)
-        hipLaunchKernelGGL((prism_volume<P, R, EB, NT, BT, true, false, false>), dim3(grid[K_VOLUME]), dim3(NT), 0, st,
-                           a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, g, eref, rho0);
+        hipLaunchKernelGGL((prism_volume_d<P, BT, false>), dim3(grid[K_VOLUME]), dim3(PrismD<P, true>::NT), 0, st,
+                           a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, mft, g, eref, rho0);
       else
         hipLaunchKernelGGL((prism_volume_mf<P, BT, false>), dim3(grid[K_VOLUME]), dim3(PrismMf<P, true>::NT), 0, st,
                            a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, mft, g, eref, rho0);
