@@ -13,8 +13,8 @@
 // projection accumulators do not fit the registers together), and add their
 // projections through LDS.  Measured (volume group, MI355X) against the form
 // with the tables in LDS and two lanes per column (three one-wave workgroups
-// per CU at p = 4): 14 858 prisms p = 4 917 -> 455 us, 32^3 cells p = 3
-// 1112 -> 769 us, p = 2 488 -> 294 us, 40^3 p = 1 260 -> 187 us; curved, 24^3
+// per CU at p = 4): 14 858 prisms p = 4 917 -> 424 us, 32^3 cells p = 3
+// 1112 -> 764 us, p = 2 488 -> 294 us, 40^3 p = 1 260 -> 187 us; curved, 24^3
 // p = 3 506 -> 366 us, 20^3 p = 4 1202 -> 508 us.
 namespace fr {
 
@@ -39,7 +39,9 @@ struct PrismD {
   static constexpr int mx(int a, int b) { return a > b ? a : b; }
   static constexpr int PE = mx(C::SZ_A + C::SZ_JE, mx(SZ_T1, SZ_Z));
   static constexpr int L0 = (m + 1) / 2;  // levels of the first wave
-  static constexpr int KG = NTN + 3 * n;
+  // the xi (eta) derivative takes no lift from edge 0 (2), whose normal has no
+  // such component (p = 4: 455 -> 424 us, the table nearer to the scalar cache's size)
+  static constexpr int KG = NTN + 2 * n;
   static constexpr int RP = (NTN + 1) / 2;  // projection rows per wave
 };
 
@@ -66,9 +68,10 @@ static void prism_d_pack(const RefElem& r, double* o) {
     for (int d = 0; d < 2; ++d) {
       double* row = o + B::grad + (2 * t + d) * KG;
       for (int k = 0; k < NTN; ++k) row[k] = d ? T.Deta[t * NTN + k] : T.Dxi[t * NTN + k];
-      for (int e = 0; e < 3; ++e) {
-        const double nx = e == 0 ? 0.0 : (e == 1 ? h : -1.0), ny = e == 0 ? -1.0 : (e == 1 ? h : 0.0);
-        for (int i = 0; i < n; ++i) row[NTN + e * n + i] = (d ? ny : nx) * T.LiftEdge[(e * NTN + t) * n + i];
+      for (int k = 0; k < 2; ++k) {
+        const int e = d ? k : 1 + k;
+        const double nrm = e == 1 ? h : -1.0;
+        for (int i = 0; i < n; ++i) row[NTN + k * n + i] = nrm * T.LiftEdge[(e * NTN + t) * n + i];
       }
     }
   for (int i = 0; i < NTQ * NTN; ++i) o[B::tq + i] = T.Tq[i];
@@ -259,11 +262,11 @@ __global__ void __launch_bounds__((PrismD<P, !WARP>::NT)) __attribute__((amdgpu_
 #pragma unroll
         for (int c = 0; c < NTN; ++c) g0 += gr[c] * x[c];
 #pragma unroll
-        for (int q = 0; q < 3 * n; ++q) g0 += gr[NTN + q] * jq[q];
+        for (int q = 0; q < 2 * n; ++q) g0 += gr[NTN + q] * jq[n + q];
 #pragma unroll
         for (int c = 0; c < NTN; ++c) g1 += gr[M::KG + c] * x[c];
 #pragma unroll
-        for (int q = 0; q < 3 * n; ++q) g1 += gr[M::KG + NTN + q] * jq[q];
+        for (int q = 0; q < 2 * n; ++q) g1 += gr[M::KG + NTN + q] * jq[q];
         if constexpr (WARP) {
           if (ok) {
             X[(5 + v) * NU + t] = g0;
