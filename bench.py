@@ -43,7 +43,7 @@ HEX_VOL_P3_FP32_TRAFFIC = (286902 * 2 + 276480) * 1024
 # device functions: the point flux f = f^e - f^v with the split energy
 # component, the normal viscous flux, the interface flux of one own flux
 # point (both sides' inviscid fluxes, Rusanov, LDG, the jump terms)
-PF_FLOP, NV_FLOP, CF_FLOP = 147, 120, 140
+PF_FLOP, NV_FLOP, CF_FLOP = 122, 98, 140
 
 NTYPE_PTS = {  # (N_u, flux points, quadrature points, faces) per element
     "hex": lambda n, m: (n ** 3, 6 * n * n, m ** 3, 6),

@@ -58,68 +58,69 @@ __device__ __forceinline__ void lds_barrier() {
 // form), q[d][v]: physical gradients d/dx_d of the conserved variables.
 // f[d][v]: component d of the flux of variable v; the energy component is
 // the split form (v H with H = E' + p' + hc0 - kap rho').
+// The gradients of velocity and internal energy are carried times rho
+// (w = rho grad v, en = rho grad e) and the one division joins the viscosity;
+// the symmetric momentum flux is formed once per pair.
 template <typename R>
 __device__ __forceinline__ void point_flux(const R u[5], const R q[3][5], const Gas<R>& g, R f[3][5]) {
   const R rho = u[0] + g.rho0, ir = rcp(rho);
   const R v[3] = {u[1] * ir, u[2] * ir, u[3] * ir};
   const R pp = g.gm1 * (u[4] - R(0.5) * (u[1] * v[0] + u[2] * v[1] + u[3] * v[2]));
   const R H = u[4] + pp + g.hc0 - g.kap * u[0];
-  // velocity gradient gv[d][i] = d v_i / d x_d
-  R gv[3][3];
-#pragma unroll
-  for (int d = 0; d < 3; ++d)
-#pragma unroll
-    for (int i = 0; i < 3; ++i) gv[d][i] = (q[d][1 + i] - v[i] * q[d][0]) * ir;
-  const R div = gv[0][0] + gv[1][1] + gv[2][2];
   const R et = (u[4] + g.eref) * ir;  // total energy per unit mass
-  R ge[3];
-#pragma unroll
-  for (int d = 0; d < 3; ++d)
-    ge[d] = (q[d][4] - et * q[d][0]) * ir - (v[0] * gv[d][0] + v[1] * gv[d][1] + v[2] * gv[d][2]);
+  const R mi = g.mu * ir, mhi = g.muh * ir;
+  R w[3][3], en[3];  // w[d][i] = rho d v_i / d x_d
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    R t[3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) t[i] = g.mu * (gv[d][i] + gv[i][d]);
-    t[d] -= (R(2) / R(3)) * g.mu * div;
+    for (int i = 0; i < 3; ++i) w[d][i] = q[d][1 + i] - v[i] * q[d][0];
+    en[d] = q[d][4] - et * q[d][0] - (v[0] * w[d][0] + v[1] * w[d][1] + v[2] * w[d][2]);
+  }
+  const R dil = (R(2) / R(3)) * mi * (w[0][0] + w[1][1] + w[2][2]);
+  R t[3][3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    t[d][d] = (mi + mi) * w[d][d] - dil;
+#pragma unroll
+    for (int i = 0; i < d; ++i) t[d][i] = t[i][d] = mi * (w[d][i] + w[i][d]);
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
     f[d][0] = u[1 + d];
+    f[d][1 + d] = u[1 + d] * v[d] - t[d][d] + pp;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) f[d][1 + i] = u[1 + d] * v[i] - t[i];
-    f[d][1 + d] += pp;
-    f[d][4] = v[d] * H - (v[0] * t[0] + v[1] * t[1] + v[2] * t[2] + g.muh * ge[d]);
+    for (int i = 0; i < d; ++i) f[d][1 + i] = f[i][1 + d] = u[1 + d] * v[i] - t[d][i];
+    f[d][4] = v[d] * H - (v[0] * t[d][0] + v[1] * t[d][1] + v[2] * t[d][2] + mhi * en[d]);
   }
 }
 
 // Normal viscous flux n . f^v (momentum x,y,z and energy; the mass
-// component is zero) at one point.
+// component is zero) at one point: with w = rho grad v the traction is
+// mu/rho (n . w + w . n - 2/3 n tr w) and the heat flux takes the normal
+// derivatives alone.
 template <typename R>
 __device__ __forceinline__ void normal_viscous(const R u[5], const R q[3][5], const R n[3], const Gas<R>& g,
                                                R V[4]) {
   const R rho = u[0] + g.rho0, ir = rcp(rho);
   const R v[3] = {u[1] * ir, u[2] * ir, u[3] * ir};
-  R gv[3][3];
+  const R mi = g.mu * ir, et = (u[4] + g.eref) * ir;
+  R w[3][3];
 #pragma unroll
   for (int d = 0; d < 3; ++d)
 #pragma unroll
-    for (int i = 0; i < 3; ++i) gv[d][i] = (q[d][1 + i] - v[i] * q[d][0]) * ir;
-  const R div = gv[0][0] + gv[1][1] + gv[2][2];
-  const R et = (u[4] + g.eref) * ir;
-  R tn[3] = {0, 0, 0}, hn = 0;
+    for (int i = 0; i < 3; ++i) w[d][i] = q[d][1 + i] - v[i] * q[d][0];
+  const R dil = (R(2) / R(3)) * (w[0][0] + w[1][1] + w[2][2]);
+  const R q0 = n[0] * q[0][0] + n[1] * q[1][0] + n[2] * q[2][0];
+  R en = n[0] * q[0][4] + n[1] * q[1][4] + n[2] * q[2][4] - et * q0;
+  R e = R(0);
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const R ge = (q[d][4] - et * q[d][0]) * ir - (v[0] * gv[d][0] + v[1] * gv[d][1] + v[2] * gv[d][2]);
-    hn += n[d] * g.muh * ge;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      R t = g.mu * (gv[d][i] + gv[i][d]);
-      if (i == d) t -= (R(2) / R(3)) * g.mu * div;
-      tn[i] += n[d] * t;
-    }
+  for (int i = 0; i < 3; ++i) {
+    const R wn = n[0] * w[0][i] + n[1] * w[1][i] + n[2] * w[2][i];
+    V[i] = mi * (wn + (n[0] * w[i][0] + n[1] * w[i][1] + n[2] * w[i][2]) - dil * n[i]);
+    en -= v[i] * wn;
+    e += v[i] * V[i];
   }
-  V[0] = tn[0];
-  V[1] = tn[1];
-  V[2] = tn[2];
-  V[3] = v[0] * tn[0] + v[1] * tn[1] + v[2] * tn[2] + hn;
+  V[3] = e + g.muh * ir * en;
 }
 
 // Normal inviscid flux f^e . n and the wave-speed bound |v.n| + c at one
