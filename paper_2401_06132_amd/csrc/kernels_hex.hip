@@ -441,9 +441,12 @@ struct HexVolLoads {
 // the face quadrature points (from the solution and corrected gradient
 // interpolated there) and stores its projection at the flux points.  Only
 // the Rusanov flux, nonlinear in the pair, is left to the interface kernel.
+//
+// The launch shape of single precision at p = 3 wants three waves per SIMD
+// (168 VGPRs; the general metric took 174 and so only two).
 template <int P, typename R, int EB, int NT, bool DIAG, bool BT, bool AA, bool SAA, bool WARP>
 __global__ void __launch_bounds__(NT)
-    hex_volume(const Seg one, const BlkRef* __restrict__ bt, const Seg* __restrict__ segs, const bool from_ust,
+    __attribute__((amdgpu_waves_per_eu(P == 3 && sizeof(R) == 4 && AA && !SAA && !WARP ? 3 : 1))) hex_volume(const Seg one, const BlkRef* __restrict__ bt, const Seg* __restrict__ segs, const bool from_ust,
                const HexOps<P, R> op, const Gas<R> g, const double eref, const double rho0) {
   // LIN: the mass flux's divergence and the linear energy-flux part come
   // from the disu kernel's L(rho v) (affine elements only)
@@ -504,18 +507,19 @@ __global__ void __launch_bounds__(NT)
   // L side (1/2 + beta)(u_nbr - u_own), R side (1/2 - beta)(u_nbr - u_own)),
   // and the corrected gradient D u + lift (eq. FR-qfinal).  With a diagonal
   // metric the J^-T scaling of eq. FR-gradcoru is applied here as well.
+  // (the axes inside the item loop, so that they share its index arithmetic)
+  for (int it = tid; it < EB * 5 * NFP; it += NT) {
+    const int le = it / (5 * NFP), r0 = it - le * (5 * NFP), v = r0 / NFP, r = r0 - v * NFP;
+    const int a = r % n, b = r / n;
+    R* X = XS(le) + v * NU;
+    const R* J = JS(le) + v * NFP + r;
 #pragma unroll
-  for (int ax = 0; ax < 3; ++ax) {
-    const int si = ax == 0 ? 1 : (ax == 1 ? n : n * n);
-    const int sa = ax == 0 ? n : 1, sb = ax == 2 ? n : n * n;
-    for (int it = tid; it < EB * 5 * NFP; it += NT) {
-      const int le = it / (5 * NFP), r0 = it - le * (5 * NFP), v = r0 / NFP, r = r0 - v * NFP;
-      const int a = r % n, b = r / n;
-      R* X = XS(le);
-      const int base = a * sa + b * sb;
+    for (int ax = 0; ax < 3; ++ax) {
+      const int si = ax == 0 ? 1 : (ax == 1 ? n : n * n);
+      const int base = ax == 0 ? n * r : (ax == 1 ? a + n * n * b : r);
       R x[n];
 #pragma unroll
-      for (int i = 0; i < n; ++i) x[i] = X[v * NU + base + i * si];
+      for (int i = 0; i < n; ++i) x[i] = X[base + i * si];
       R xm = R(0), xp = R(0);
 #pragma unroll
       for (int i = 0; i < n; ++i) {
@@ -523,15 +527,15 @@ __global__ void __launch_bounds__(NT)
         xp += op.rb[i] * x[i];
       }
       const int im = cFR[le * 6 + 2 * ax].info, ip = cFR[le * 6 + 2 * ax + 1].info;
-      const R jm = ((im & 1) ? R(0.5) + g.beta : R(0.5) - g.beta) * (JS(le)[((2 * ax) * 5 + v) * NFP + r] - xm);
-      const R jp = ((ip & 1) ? R(0.5) + g.beta : R(0.5) - g.beta) * (JS(le)[((2 * ax + 1) * 5 + v) * NFP + r] - xp);
+      const R jm = ((im & 1) ? R(0.5) + g.beta : R(0.5) - g.beta) * (J[2 * ax * 5 * NFP] - xm);
+      const R jp = ((ip & 1) ? R(0.5) + g.beta : R(0.5) - g.beta) * (J[(2 * ax + 1) * 5 * NFP] - xp);
       const R sc = DIAG ? sMet[le][4 * ax] : R(1);
 #pragma unroll
       for (int i = 0; i < n; ++i) {
         R s = op.liftR[i] * jp - op.liftL[i] * jm;
 #pragma unroll
         for (int c = 0; c < n; ++c) s += op.D[i][c] * x[c];
-        X[(5 + ax * 5 + v) * NU + base + i * si] = sc * s;
+        X[(5 + ax * 5) * NU + base + i * si] = sc * s;
       }
     }
   }
@@ -763,25 +767,23 @@ __global__ void __launch_bounds__(NT)
   // Over region A (TOX) every thread reads its x rows into registers before
   // a barrier and writes T1 after it.
   if constexpr (TOX) {
-    constexpr int NIT = (EB * 20 * NFP + NT - 1) / NT;
+    constexpr int NX = EB * 20 * NFP, NIT = (NX + NT - 1) / NT;
     R x[NIT][n];
+    int tof[NIT];  // where the line's first value goes in T1
 #pragma unroll
     for (int k = 0; k < NIT; ++k) {
-      const int it = tid + k * NT;
-      if (it < EB * 20 * NFP) {
-        const int le = it / (20 * NFP), r0 = it - le * (20 * NFP), fld = r0 / NFP, r = r0 - fld * NFP;
+      const int it = tid + k * NT, itc = it < NX ? it : 0;
+      const int q = itc / NFP, r = itc - q * NFP, le = q / 20;  // q = 20 le + field
+      const R* X = smem + q * NU + le * (PE - 20 * NU) + n * r;
+      tof[k] = q * (m * C::TPS) + le * (PE - 20 * m * C::TPS) + (r % n) * n + r / n;
 #pragma unroll
-        for (int i = 0; i < n; ++i) x[k][i] = XS(le)[fld * NU + i + n * r];
-      }
+      for (int i = 0; i < n; ++i) x[k][i] = X[i];
     }
     lds_barrier();
 #pragma unroll
     for (int k = 0; k < NIT; ++k) {
-      const int it = tid + k * NT;
-      if (it < EB * 20 * NFP) {
-        const int le = it / (20 * NFP), r0 = it - le * (20 * NFP), fld = r0 / NFP, r = r0 - fld * NFP;
-        const int j = r % n, l = r / n;
-        R* T = TS(le) + (fld * m) * C::TPS + j * n + l;
+      if (tid + k * NT < NX) {
+        R* T = smem + tof[k];
 #pragma unroll
         for (int a = 0; a < m; ++a) {
           R s = R(0);
