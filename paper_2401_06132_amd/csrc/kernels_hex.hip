@@ -270,10 +270,11 @@ __global__ void __launch_bounds__(NT) hex_disu(const Seg one, const BlkRef* __re
 // The footprint is the largest of A + B, T1 and Z (p = 3: 2160 values
 // instead of 3440 with separate regions).  Measured at 48^3 (volume group):
 // FP32 p = 3 with 7 elements per workgroup 0.736 -> 0.627 ms, FP32 p = 4
-// 1.51 -> 1.24 ms, FP64 p = 3 1.89 -> 1.51 ms.  At p = 4 in FP64, with
-// surface-flux AA or curved, T1 stays after region A and Y after Z (the
-// footprint is the larger of A + B + T1 and Z + Y): the x rows held in
-// registers there spill (FP64: 4.29 -> 4.54 ms).
+// 1.51 -> 1.24 ms, FP64 p = 3 1.89 -> 1.51 ms.  At p = 4 in FP64, curved or
+// with surface-flux AA this holds only since the z levels of the column phase
+// are a loop and the x-sweep addresses are formed once (before, the x rows
+// spilled and T1 had a region of its own): 32^3 FP64 1.01 -> 0.89 ms, FP32
+// with surface-flux AA 0.69 -> 0.58 ms, curved FP32 0.60 -> 0.50 ms.
 template <int P, bool LIN>
 struct HexVol {
   static constexpr int n = P + 1, m = P + 3, NU = n * n * n, NFP = n * n;
@@ -292,16 +293,10 @@ struct HexVol {
   // first tangential axis [2][20][m][n], viscous flux at the face
   // quadrature points [2][4][m][m]
   static constexpr int SZ_ST = 2 * 20 * m * n, SZ_S = SZ_ST + 2 * 4 * m * m;
-  // T1 over region A and Y inside Z (TOX), or T1 after region A and Y after
-  // Z; at p = 4 in FP64, with surface-flux AA (SAA) or curved (WARP) the
-  // registers that hold the x rows across the barrier spill
-  template <typename R, bool SAA, bool WARP>
-  static constexpr bool tox() { return !(P >= 4 && (sizeof(R) == 8 || SAA || WARP)); }
   // per element with flux anti-aliasing; SAA: with surface-flux AA staging
-  static constexpr int per_elem(bool SAA, bool TOX) {
-    const int b0 = SAA && SZ_S > SZ_J ? SZ_S : SZ_J;
-    const int b = TOX || b0 > SZ_T1 ? b0 : SZ_T1;
-    const int t = TOX ? (SZ_T1 > SZ_Z ? SZ_T1 : SZ_Z) : SZ_Z + SZ_Y;
+  static constexpr int per_elem(bool SAA) {
+    const int b = SAA && SZ_S > SZ_J ? SZ_S : SZ_J;
+    const int t = SZ_T1 > SZ_Z ? SZ_T1 : SZ_Z;
     return SZ_A + b > t ? SZ_A + b : t;
   }
 };
@@ -443,10 +438,22 @@ struct HexVolLoads {
 // the Rusanov flux, nonlinear in the pair, is left to the interface kernel.
 //
 // The launch shape of single precision at p = 3 wants three waves per SIMD
-// (168 VGPRs; the general metric took 174 and so only two).
+// (168 VGPRs; the general metric took 174 and so only two).  Double precision
+// at p = 2 wants two (256 VGPRs; left to itself it takes 259 to 266 and so only
+// one: 40^3 400 -> 298 us, with surface-flux AA 685 -> 522 us, for 3 to 9
+// values spilled).  p = 3 needs about 320 and p = 4 about 390: held to 256 they
+// spill in the level loop (p = 3: 438 -> 583 us).
+template <int P, typename R, bool AA, bool SAA, bool WARP>
+constexpr int hex_vol_waves() {
+  if (P == 3 && sizeof(R) == 4 && AA && !SAA && !WARP) return 3;
+  if (P == 2 && sizeof(R) == 8 && AA && !WARP) return 2;
+  return 1;
+}
+
 template <int P, typename R, int EB, int NT, bool DIAG, bool BT, bool AA, bool SAA, bool WARP>
 __global__ void __launch_bounds__(NT)
-    __attribute__((amdgpu_waves_per_eu(P == 3 && sizeof(R) == 4 && AA && !SAA && !WARP ? 3 : 1))) hex_volume(const Seg one, const BlkRef* __restrict__ bt, const Seg* __restrict__ segs, const bool from_ust,
+    __attribute__((amdgpu_waves_per_eu(hex_vol_waves<P, R, AA, SAA, WARP>())))
+    hex_volume(const Seg one, const BlkRef* __restrict__ bt, const Seg* __restrict__ segs, const bool from_ust,
                const HexOps<P, R> op, const Gas<R> g, const double eref, const double rho0) {
   // LIN: the mass flux's divergence and the linear energy-flux part come
   // from the disu kernel's L(rho v) (affine elements only)
@@ -454,8 +461,7 @@ __global__ void __launch_bounds__(NT)
   using C = HexVol<P, LIN>;
   constexpr int n = C::n, m = C::m, NU = C::NU, NFP = C::NFP, NVF = C::NVF, V0 = C::V0;
   constexpr int SZ_BN = SAA && C::SZ_S > C::SZ_J ? C::SZ_S : C::SZ_J;  // region B without AA
-  constexpr bool TOX = C::template tox<R, SAA, WARP>();
-  constexpr int PE = AA ? C::per_elem(SAA, TOX) : C::SZ_A + SZ_BN;
+  constexpr int PE = AA ? C::per_elem(SAA) : C::SZ_A + SZ_BN;
   static_assert(EB * m * m <= NT, "one quadrature column per thread");
   __shared__ R smem[EB * PE];
   __shared__ R sMet[EB][10];
@@ -475,9 +481,9 @@ __global__ void __launch_bounds__(NT)
   const R* __restrict__ met = (const R*)sg.met;
   const int E = sg.E, slot_base = sg.slot_base, tid = threadIdx.x;
 #define XS(le) (smem + (le)*PE)            /* [20][NU]                     */
-#define YS(le) (smem + (le)*PE + (TOX ? 0 : C::SZ_Z)) /* [2][NVF][m][YB][n] */
+#define YS(le) (smem + (le)*PE)            /* [2][NVF][m][m][n]            */
 #define JS(le) (smem + (le)*PE + C::SZ_A)  /* [6][5][NFP] neighbour u^f    */
-#define TS(le) (smem + (le)*PE + (TOX ? 0 : C::SZ_A)) /* [20][m][TPS]      */
+#define TS(le) (smem + (le)*PE)            /* [20][m][TPS]                 */
 #define ZS(le) (smem + (le)*PE)            /* [3][NVF][m][m][n]            */
 #define SS(le) (smem + (le)*PE + C::SZ_A)  /* [2][20][m][n], [2][4][m][m]  */
 
@@ -764,9 +770,9 @@ __global__ void __launch_bounds__(NT)
     return;
   }
   // phase 3b: x interpolation of the 20 fields (first factor of M7 / M10).
-  // Over region A (TOX) every thread reads its x rows into registers before
-  // a barrier and writes T1 after it.
-  if constexpr (TOX) {
+  // Every thread reads its x rows into registers before a barrier and writes
+  // T1, which lies over them, after it.
+  {
     constexpr int NX = EB * 20 * NFP, NIT = (NX + NT - 1) / NT;
     R x[NIT][n];
     int tof[NIT];  // where the line's first value goes in T1
@@ -791,22 +797,6 @@ __global__ void __launch_bounds__(NT)
           for (int i = 0; i < n; ++i) s += op.I[a][i] * x[k][i];
           T[a * C::TPS] = s;
         }
-      }
-    }
-  } else {
-    for (int it = tid; it < EB * 20 * NFP; it += NT) {
-      const int le = it / (20 * NFP), r0 = it - le * (20 * NFP), fld = r0 / NFP, r = r0 - fld * NFP;
-      const int j = r % n, l = r / n;
-      R x[n];
-#pragma unroll
-      for (int i = 0; i < n; ++i) x[i] = XS(le)[fld * NU + i + n * r];
-      R* T = TS(le) + (fld * m) * C::TPS + j * n + l;
-#pragma unroll
-      for (int a = 0; a < m; ++a) {
-        R s = R(0);
-#pragma unroll
-        for (int i = 0; i < n; ++i) s += op.I[a][i] * x[i];
-        T[a * C::TPS] = s;
       }
     }
   }
@@ -849,11 +839,9 @@ __global__ void __launch_bounds__(NT)
     // the z levels in a loop (not unrolled), so that the operator entries of
     // one level are live at a time.  Fully unrolled, the FP64 constants of
     // all levels spill out of the scalar registers (p = 3 at 48^3: 1.81 ->
-    // 1.49 ms as a loop); in single precision the loop is 2% faster at p = 3
-    // and 4 (smaller code).  FP64 at p = 4 stays unrolled (the loop was 5%
-    // slower there).
-    constexpr int KQ_UNROLL = sizeof(R) == 8 && P >= 4 ? m : 1;
-#pragma unroll KQ_UNROLL
+    // 1.49 ms as a loop; p = 4 at 32^3: 1.24 -> 1.03 ms); in single precision
+    // the loop is 2% faster at p = 3 and 4 (smaller code).
+#pragma unroll 1
     for (int kq = 0; kq < m; ++kq) {
       R u[5], q[3][5], f[3][5];
 #pragma unroll
@@ -893,10 +881,9 @@ __global__ void __launch_bounds__(NT)
   }
   lds_barrier();
 
-  // phase 5: y projection: X' = P_y X, Y' = AP_y Y + P_y Z.  Inside Z
-  // (TOX), Y[d][v][a][j][l] takes the place of Z[d][v][a][j][l], which only
-  // this thread reads (into registers, before it writes).
-  constexpr int YB = TOX ? m : n;
+  // phase 5: y projection: X' = P_y X, Y' = AP_y Y + P_y Z.
+  // Y[d][v][a][j][l] takes the place of Z[d][v][a][j][l], which only this
+  // thread reads (into registers, before it writes).
   for (int it = tid; it < EB * NVF * m * n; it += NT) {
     const int le = it / (NVF * m * n), r0 = it - le * (NVF * m * n);
     const int v = r0 / (m * n), r1 = r0 - v * (m * n), a = r1 / n, l = r1 - a * n;
@@ -918,8 +905,8 @@ __global__ void __launch_bounds__(NT)
         sy += op.AP[j][b] * zy[b];
         sy += op.Pj[j][b] * zz[b];
       }
-      Y[(((0 * NVF + v) * m + a) * YB + j) * n + l] = sx;
-      Y[(((1 * NVF + v) * m + a) * YB + j) * n + l] = sy;
+      Y[(((0 * NVF + v) * m + a) * m + j) * n + l] = sx;
+      Y[(((1 * NVF + v) * m + a) * m + j) * n + l] = sy;
     }
   }
   lds_barrier();
@@ -940,8 +927,8 @@ __global__ void __launch_bounds__(NT)
     R y0[m], y1[m];
 #pragma unroll
     for (int a = 0; a < m; ++a) {
-      y0[a] = Y[(((0 * NVF + v) * m + a) * YB + j) * n + l];
-      y1[a] = Y[(((1 * NVF + v) * m + a) * YB + j) * n + l];
+      y0[a] = Y[(((0 * NVF + v) * m + a) * m + j) * n + l];
+      y1[a] = Y[(((1 * NVF + v) * m + a) * m + j) * n + l];
     }
 #pragma unroll
     for (int i = 0; i < n; ++i) {
@@ -1273,19 +1260,22 @@ template <> struct HexLaunch<3, true> { static constexpr int EB = 1, NT = 64; };
 template <> struct HexLaunch<4, true> { static constexpr int EB = 1, NT = 64; };    // 49
 
 // with flux anti-aliasing (AA) the footprint of the overlaid LDS regions
-// fits more elements per workgroup in FP32.  BASE: the affine kernel without
-// surface-flux AA.  p = 3: 6 elements per 256 threads (216 quadrature
+// fits more elements per workgroup in FP32.  Affine without surface-flux
+// AA, p = 3: 6 elements per 256 threads (216 quadrature
 // columns); at 168 VGPRs and 48 KB of LDS three workgroups share a CU (three
 // waves per SIMD): 0.59 -> 0.51 ms at 48^3 against 7 elements (two
 // workgroups per CU; 5 elements: 0.54 ms).  p = 4: 5 elements per 256
 // threads (245 columns): 1.18 -> 1.13 ms against one-element one-wave
-// groups.  The surface-AA and curved kernels keep 7 elements (p = 3) and
-// one-wave groups (p = 4).
-template <int P, bool DBL, bool AA, bool BASE = true>
+// groups (curved at 32^3: 0.494 -> 0.486 ms).  The surface-AA and curved
+// kernels keep 7 elements at p = 3, surface AA one-wave groups at p = 4 (18 KB
+// per element: five would leave one workgroup per CU).
+template <int P, bool DBL, bool AA, bool SAA = false, bool WARP = false>
 struct HexVolLaunch : HexLaunch<P, DBL> {};
-template <> struct HexVolLaunch<3, false, true, true> { static constexpr int EB = 6, NT = 256; };
-template <> struct HexVolLaunch<3, false, true, false> { static constexpr int EB = 7, NT = 256; };
-template <> struct HexVolLaunch<4, false, true, true> { static constexpr int EB = 5, NT = 256; };
+template <> struct HexVolLaunch<3, false, true, false, false> { static constexpr int EB = 6, NT = 256; };
+template <> struct HexVolLaunch<3, false, true, true, false> { static constexpr int EB = 7, NT = 256; };
+template <> struct HexVolLaunch<3, false, true, false, true> { static constexpr int EB = 7, NT = 256; };
+template <> struct HexVolLaunch<4, false, true, false, false> { static constexpr int EB = 5, NT = 256; };
+template <> struct HexVolLaunch<4, false, true, false, true> { static constexpr int EB = 5, NT = 256; };
 
 // elements per workgroup of the disu kernel (256 threads; at 48^3, FP32
 // p = 3: 4 elements 0.099 ms, 8 elements 0.107 ms, 16 elements 0.142 ms)
@@ -1304,7 +1294,7 @@ template <int P, typename R, bool BT, bool DIAG, bool AA, bool SAA, bool WARP = 
 static void hex_volume_launch(const TypeArgs& a, int nb, const HexOps<P, R>& op, const Gas<R>& g, double eref,
                               hipStream_t st) {
   constexpr bool dbl = sizeof(R) == 8;
-  using L = HexVolLaunch<P, dbl, AA, !SAA && !WARP>;
+  using L = HexVolLaunch<P, dbl, AA, SAA, WARP>;
   constexpr int EB = L::EB, NT = L::NT;
   hipLaunchKernelGGL((hex_volume<P, R, EB, NT, DIAG, BT, AA, SAA, WARP>), dim3(nb), dim3(NT), 0, st, a.one,
                      a.bt[K_VOLUME], a.segs, a.from_ust, op, g, eref, a.gas->rho_ref);
@@ -1384,8 +1374,10 @@ template <int P, typename R>
 static hipError_t hex_rhs_t(const TypeArgs& a, hipStream_t st) {
   constexpr bool dbl = sizeof(R) == 8;
   const int ebs[3] = {HEX_DISU_EB,
-                      a.aa ? (a.saa || a.warp ? HexVolLaunch<P, dbl, true, false>::EB : HexVolLaunch<P, dbl, true>::EB)
-                           : HexVolLaunch<P, dbl, false>::EB,
+                      !a.aa    ? HexVolLaunch<P, dbl, false>::EB
+                      : a.warp ? HexVolLaunch<P, dbl, true, false, true>::EB
+                      : a.saa  ? HexVolLaunch<P, dbl, true, true>::EB
+                               : HexVolLaunch<P, dbl, true>::EB,
                       a.saa ? HexSurf<P, dbl, true>::EB : HexSurf<P, dbl>::EB};
   const bool bt = a.bt[0] && a.bt[1] && a.bt[2] && a.segs;
   int grid[3];
@@ -1406,8 +1398,8 @@ static int hex_surf_elems(bool d, bool saa) {
 template <int P>
 static int hex_vol_elems(bool d, bool aa, bool saa) {
   if (!aa) return d ? HexVolLaunch<P, true, false>::EB : HexVolLaunch<P, false, false>::EB;
-  return d ? (saa ? HexVolLaunch<P, true, true, false>::EB : HexVolLaunch<P, true, true>::EB)
-           : (saa ? HexVolLaunch<P, false, true, false>::EB : HexVolLaunch<P, false, true>::EB);
+  return d ? (saa ? HexVolLaunch<P, true, true, true>::EB : HexVolLaunch<P, true, true>::EB)
+           : (saa ? HexVolLaunch<P, false, true, true>::EB : HexVolLaunch<P, false, true>::EB);
 }
 
 int hex_block_elems(int p, int prec, int k, bool aa, bool saa) {
