@@ -12,9 +12,11 @@
 // needs ceil(R/4) K / 16 registers and no scalar or LDS operand traffic.
 // The products are fused multiply-adds in single precision in the order of
 // k, the same bits as a loop of fmaf (checked over the lane layout, the
-// broadcasts and random operands).  Measured rate on the MI355X: 9.7 cycles
-// (at 2.4 GHz nominal) for 4 x 64 multiply-adds against 18.2 for four vector
-// FMAs, and the two pipes overlap between waves in different phases.
+// broadcasts and random operands).  Measured on the MI355X: 8.9 cycles for
+// 4 x 64 multiply-adds against 4 x 4.8 for vector FMAs.  The two do not
+// overlap (a SIMD with one wave of each kind takes the sum of their times:
+// single-precision matrix and vector instructions share the ALUs), so the gain
+// is this rate and the operands that no longer come through LDS.
 //
 // The instruction ignores EXEC: every call below sits in wave-uniform
 // control flow, with out-of-range items clamped to a valid one and dropped
