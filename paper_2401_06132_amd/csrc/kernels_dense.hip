@@ -173,10 +173,15 @@ __device__ __forceinline__ void const_flux(const float* __restrict__ ub, const R
 //   L(rho v) = sum_d Lv_d (S m)_d,  Lv_d = D_d (tetrahedra: the strong form
 //   (M1 - M3 M2) plus the lift of the own trace), Lv_d = Ku_d + M3 n_d M0
 //   (pyramids: their weak form plus the lift of the own trace).
+// Both are packed for the matrix cores: per 16-row tile and k-step of four
+// (zero past the rows and past k; k of the second runs over (d, point)), the
+// 64 lanes' values A[l mod 16][l / 16].
 template <int ET, int P>
 struct DenseDisu {
   using C = DenseCfg<ET, P>;
-  static constexpr int O_M0 = 0, O_LV = C::NF * C::NU, SIZE = O_LV + 3 * C::NU * C::NU;
+  static constexpr int RT0 = (C::NF + 15) / 16, KS0 = (C::NU + 3) / 4;      // M0
+  static constexpr int RT1 = (C::NU + 15) / 16, KS1 = (3 * C::NU + 3) / 4;  // [Lv_0 | Lv_1 | Lv_2]
+  static constexpr int O_M0 = 0, O_LV = RT0 * KS0 * 64, SIZE = O_LV + RT1 * KS1 * 64;
 };
 
 // byte offset of the double-precision block behind the table
@@ -189,6 +194,14 @@ constexpr size_t dense_disu_offset(size_t rs) {
 // single precision stores a float base per face (its value at the face's
 // first flux point) and the deviations.  LIN: L(rho v) to row 0 of the
 // volume residual.
+// Both products run on v_mfma_f64_16x16x4f64.  With one operator row per
+// thread each multiply-add took an LDS value and every fifth an operator value
+// from the vector cache, and those bound the kernel, not HBM; a tile takes one
+// of each per 16.  Sums in double precision as before.  196 608 tetrahedra p = 3
+// / 4: 215 / 489 -> 177 / 339 us (p = 3 moves 0.36 GB: 70 us at the copy rate), 82 944
+// pyramids 169 / 435 -> 131 / 292; p <= 2 within 4%.  6 or 12 elements per
+// workgroup (30 of 32, 60 of 64 columns instead of 40 of 48) are within 5%
+// either way, 16 are slower from p = 4 and pyramids p = 3 on (LDS).
 template <int ET, int P, typename R, int EB, int NT>
 __global__ void __launch_bounds__(NT) dense_disu(const Seg sg, const bool from_ust, const double* __restrict__ ops,
                                                const double eref, const double rho0, const bool lin) {
@@ -196,10 +209,13 @@ __global__ void __launch_bounds__(NT) dense_disu(const Seg sg, const bool from_u
   using DD = DenseDisu<ET, P>;
   constexpr int NU = C::NU, NF = C::NF, NFACE = C::NFACE;
   constexpr bool FB = sizeof(R) == 4;
+  constexpr int FS = NF | 1, NC = EB * 5, CT = (NC + 15) / 16, NW = NT / 64;
+  typedef double v4d __attribute__((ext_vector_type(4)));
   __shared__ double sU[EB * 5 * NU];
-  __shared__ double sF[EB * 5 * NF];
+  __shared__ double sF[EB * 5 * FS];
   __shared__ double sS[EB][9];
   const int e0 = blockIdx.x * EB, E = sg.E, tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid & 63, lj = lane & 15, lk = lane >> 4;
   const double* __restrict__ U = from_ust ? sg.ust : sg.U;
   R* __restrict__ Uf = (R*)sg.Uf;
   if (lin && tid < EB * 9) {
@@ -229,13 +245,24 @@ __global__ void __launch_bounds__(NT) dense_disu(const Seg sg, const bool from_u
     }
   }
   lds_barrier();
-  for (int it = tid; it < EB * NF; it += NT) {
-    // element fastest: the lanes of a wave share operator rows (EB lanes a row)
-    const int fp = it / EB, le = it - fp * EB;
-    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    row_cols<NU, 5>(ops + DD::O_M0 + fp * NU, sU + le * 5 * NU, NU, acc);
+  // M0: 16 x 16 tiles of (flux points) x (element, variable) columns; the
+  // instruction ignores EXEC, so a column or k past the end reads a valid
+  // value (of the same column: the operator is zero there) and is dropped
+  for (int pr = wave; pr < DD::RT0 * CT; pr += NW) {
+    const int rt = pr / CT, col = (pr - rt * CT) * 16 + lj;
+    const double* A = ops + DD::O_M0 + rt * DD::KS0 * 64 + lane;
+    const double* B = sU + (col < NC ? col : 0) * NU;
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int v = 0; v < 5; ++v) sF[(le * 5 + v) * NF + fp] = acc[v];
+    for (int ks = 0; ks < DD::KS0; ++ks) {
+      const int k = 4 * ks + lk;
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[ks * 64], B[k < NU ? k : NU - 1], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = rt * 16 + lk + 4 * r;
+      if (col < NC && row < NF) sF[col * FS + row] = acc[r];
+    }
   }
   lds_barrier();
   for (int it = tid; it < EB * 5 * NF; it += NT) {
@@ -243,12 +270,12 @@ __global__ void __launch_bounds__(NT) dense_disu(const Seg sg, const bool from_u
     if (e >= E) continue;
     const int f = C::face_of(fp), t = C::point_of(fp);
     const size_t slot = (size_t)(sg.slot_base + e * NFACE + f);
-    const double x = sF[(le * 5 + v) * NF + fp];
+    const double x = sF[(le * 5 + v) * FS + fp];
     if constexpr (FB) {
       // the face's first flux point: the base square's first point, or a
       // triangle's first node
       const int fp0 = (C::PYR && f == 0) ? 0 : C::NB + (f - int(C::PYR)) * C::NTN;
-      const float b = float(sF[(le * 5 + v) * NF + fp0]);
+      const float b = float(sF[(le * 5 + v) * FS + fp0]);
       Uf[(size_t)(sg.po_base + e * NF + fp - t) * 5 + v * C::fsz(f) + t] = R(x - double(b));
       if (t == 0) sg.Ub[slot * 5 + v] = b;
     } else {
@@ -266,14 +293,22 @@ __global__ void __launch_bounds__(NT) dense_disu(const Seg sg, const bool from_u
   }
   lds_barrier();
   R* __restrict__ Rp = (R*)sg.Rp;
-  for (int it = tid; it < EB * NU; it += NT) {
-    const int s = it / EB, le = it - s * EB, e = e0 + le;
-    if (e >= E) continue;
-    double acc[1] = {0.0};
+  constexpr int ET1 = (EB + 15) / 16;
+  for (int pr = wave; pr < DD::RT1 * ET1; pr += NW) {
+    const int rt = pr / ET1, le = (pr - rt * ET1) * 16 + lj, e = e0 + le;
+    const double* A = ops + DD::O_LV + rt * DD::KS1 * 64 + lane;
+    const double* B = sU + (le < EB ? le : 0) * 5 * NU + NU;
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int d = 0; d < 3; ++d)
-      row_cols<NU, 1>(ops + DD::O_LV + (d * NU + s) * NU, sU + le * 5 * NU + (1 + d) * NU, NU, acc);
-    Rp[(size_t)e * 5 * NU + s] = R(acc[0]);
+    for (int ks = 0; ks < DD::KS1; ++ks) {
+      const int k = 4 * ks + lk;
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[ks * 64], B[k < 3 * NU ? k : 3 * NU - 1], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = rt * 16 + lk + 4 * r;
+      if (le < EB && e < E && row < NU) Rp[(size_t)e * 5 * NU + row] = R(acc[r]);
+    }
   }
 }
 
@@ -1297,7 +1332,11 @@ static void pack_disu(const RefElem& r, double* o) {
   using C = DenseCfg<ET, P>;
   using DD = DenseDisu<ET, P>;
   constexpr int NU = C::NU, NF = C::NF;
-  for (int i = 0; i < NF * NU; ++i) o[DD::O_M0 + i] = r.M0[i];
+  for (int i = 0; i < DD::SIZE; ++i) o[i] = 0.0;
+  // row i, column k of an operator of KS k-steps: tile i / 16, lane (i mod 16) + 16 (k mod 4)
+  const auto at = [](int i, int k, int KS) { return ((i / 16) * KS + k / 4) * 64 + (k % 4) * 16 + i % 16; };
+  for (int i = 0; i < NF; ++i)
+    for (int u = 0; u < NU; ++u) o[DD::O_M0 + at(i, u, DD::KS0)] = r.M0[i * NU + u];
   for (int d = 0; d < 3; ++d)
     for (int s = 0; s < NU; ++s)
       for (int u = 0; u < NU; ++u) {
@@ -1309,7 +1348,7 @@ static void pack_disu(const RefElem& r, double* o) {
         } else {
           acc = r.Dg[(d * NU + s) * NU + u];
         }
-        o[DD::O_LV + (d * NU + s) * NU + u] = (double)acc;
+        o[DD::O_LV + at(s, d * NU + u, DD::KS1)] = (double)acc;
       }
 }
 

@@ -1,0 +1,39 @@
+"""The first kernel group of tetrahedra and pyramids (double-precision matrix
+cores) at its tiles' edges: less than one workgroup of eight elements, a
+remainder, several workgroups; every order's remainders of 16 rows and four
+k-steps; against the oracle in extended precision.  Tolerances: FP64 1e-12, the
+FP32 floor of the precision split 2e-5."""
+
+import numpy as np
+import pytest
+
+import paper_2401_06132_amd as frmi
+from oracle.mesh import Mesh
+from oracle.rhs import Params, rhs as oracle_rhs
+from paper_2401_06132_amd import inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("kind", ["tet", "pyr"])
+@pytest.mark.parametrize("dims,p", [(d, p) for p in (1, 2, 3, 4) for d in ((1, 1, 1), (1, 2, 2))])
+def test_tile_edges(dims, p, kind, prec):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("disu case", dims, p, kind, prec, flush=True)
+    m = Mesh(*dims, p, kind)
+    U = inputs.element_state([m.upts_coords(t) for t in m.types], seed=17)
+    ref = oracle_rhs(m, {t: u.astype(np.longdouble) for t, u in zip(m.types, U)}, Params(pref=inputs.P0),
+                     dtype=np.longdouble)
+    s = frmi.Solver(dims, p, kind, prec=prec, pref=inputs.P0, rho_ref=inputs.RHO0)
+    u = torch.from_numpy(np.concatenate([x.reshape(-1) for x in U])).cuda()
+    du = torch.empty_like(u)
+    frmi.fill_lds(float("nan"))
+    s.rhs(u, du)
+    torch.cuda.synchronize()
+    err = np.max([(np.abs(g - ref[t]).max(axis=(0, 2)) / np.abs(ref[t]).max(axis=(0, 2))).astype(np.float64)
+                  for g, t in zip(s.split(du.cpu().numpy()), m.types)], axis=0)
+    print("rel err per variable", err, flush=True)
+    assert np.all(err < (1e-12 if prec == "fp64" else 2e-5)), err
