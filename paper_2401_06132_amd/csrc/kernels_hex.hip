@@ -274,7 +274,9 @@ __global__ void __launch_bounds__(NT) hex_disu(const Seg one, const BlkRef* __re
 // with surface-flux AA this holds only since the z levels of the column phase
 // are a loop and the x-sweep addresses are formed once (before, the x rows
 // spilled and T1 had a region of its own): 32^3 FP64 1.01 -> 0.89 ms, FP32
-// with surface-flux AA 0.69 -> 0.58 ms, curved FP32 0.60 -> 0.50 ms.
+// with surface-flux AA 0.69 -> 0.58 ms, curved FP32 0.60 -> 0.50 ms.  Five
+// workgroups instead of two share a CU then; where there is only one per CU the
+// longer x sweep shows (FP64 p = 4: 5^3 23 -> 27 us, 10^3 47 -> 31 us).
 template <int P, bool LIN>
 struct HexVol {
   static constexpr int n = P + 1, m = P + 3, NU = n * n * n, NFP = n * n;
