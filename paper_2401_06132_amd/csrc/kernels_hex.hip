@@ -274,9 +274,9 @@ __global__ void __launch_bounds__(NT) hex_disu(const Seg one, const BlkRef* __re
 // with surface-flux AA this holds only since the z levels of the column phase
 // are a loop and the x-sweep addresses are formed once (before, the x rows
 // spilled and T1 had a region of its own): 32^3 FP64 1.01 -> 0.89 ms, FP32
-// with surface-flux AA 0.69 -> 0.58 ms, curved FP32 0.60 -> 0.50 ms.  Five
-// workgroups instead of two share a CU then; where there is only one per CU the
-// longer x sweep shows (FP64 p = 4: 5^3 23 -> 27 us, 10^3 47 -> 31 us).
+// with surface-flux AA 0.69 -> 0.58 ms, curved FP32 0.60 -> 0.50 ms.  In
+// FP64 at p = 4 four workgroups share a CU then (one wave per SIMD: 384
+// registers) instead of three (49 KB of LDS each).
 template <int P, bool LIN>
 struct HexVol {
   static constexpr int n = P + 1, m = P + 3, NU = n * n * n, NFP = n * n;
@@ -886,29 +886,72 @@ __global__ void __launch_bounds__(NT)
   // phase 5: y projection: X' = P_y X, Y' = AP_y Y + P_y Z.
   // Y[d][v][a][j][l] takes the place of Z[d][v][a][j][l], which only this
   // thread reads (into registers, before it writes).
-  for (int it = tid; it < EB * NVF * m * n; it += NT) {
-    const int le = it / (NVF * m * n), r0 = it - le * (NVF * m * n);
-    const int v = r0 / (m * n), r1 = r0 - v * (m * n), a = r1 / n, l = r1 - a * n;
-    const R* Z = ZS(le);
-    R zx[m], zy[m], zz[m];
+  if constexpr (2 * n * m * int(sizeof(R)) / 4 > 96 && !SAA) {
+    // The two operators' entries do not fit the scalar registers together
+    // (FP64 p = 4: 140 of about 100).  A loop over the lines then reads them
+    // back from vector lanes at each line, 406 lane reads for 105
+    // multiply-adds; one row of both (14 entries), applied to all of the
+    // thread's lines, fits.  This phase of one element 10 000 -> 4 000 cycles, the
+    // kernel at 5^3 25.8 -> 23.0 us, at 33^3 889 -> 796, curved 31^3 971 ->
+    // 902.  With surface-flux AA the loop does not spill (4 400 cycles), and
+    // this form moves spills into its face phases (33^3 1399 -> 1488 us).
+    constexpr int NY = EB * NVF * m * n, NIT = (NY + NT - 1) / NT;
+    R zx[NIT][m], zy[NIT][m], zz[NIT][m];
+    R* Y[NIT];
 #pragma unroll
-    for (int b = 0; b < m; ++b) {
-      zx[b] = Z[(((0 * NVF + v) * m + a) * m + b) * n + l];
-      zy[b] = Z[(((1 * NVF + v) * m + a) * m + b) * n + l];
-      zz[b] = Z[(((2 * NVF + v) * m + a) * m + b) * n + l];
-    }
-    R* Y = YS(le);
-#pragma unroll
-    for (int j = 0; j < n; ++j) {
-      R sx = R(0), sy = R(0);
+    for (int k = 0; k < NIT; ++k) {
+      const int it = tid + k * NT < NY ? tid + k * NT : 0;
+      const int le = it / (NVF * m * n), r0 = it - le * (NVF * m * n);
+      const int v = r0 / (m * n), r1 = r0 - v * (m * n), a = r1 / n, l = r1 - a * n;
+      Y[k] = YS(le) + (v * m + a) * m * n + l;
 #pragma unroll
       for (int b = 0; b < m; ++b) {
-        sx += op.Pj[j][b] * zx[b];
-        sy += op.AP[j][b] * zy[b];
-        sy += op.Pj[j][b] * zz[b];
+        zx[k][b] = Y[k][b * n];
+        zy[k][b] = Y[k][NVF * m * m * n + b * n];
+        zz[k][b] = Y[k][2 * NVF * m * m * n + b * n];
       }
-      Y[(((0 * NVF + v) * m + a) * m + j) * n + l] = sx;
-      Y[(((1 * NVF + v) * m + a) * m + j) * n + l] = sy;
+    }
+#pragma unroll 1
+    for (int j = 0; j < n; ++j)
+#pragma unroll
+      for (int k = 0; k < NIT; ++k) {
+        R sx = R(0), sy = R(0);
+#pragma unroll
+        for (int b = 0; b < m; ++b) {
+          sx += op.Pj[j][b] * zx[k][b];
+          sy += op.AP[j][b] * zy[k][b];
+          sy += op.Pj[j][b] * zz[k][b];
+        }
+        if (tid + k * NT < NY) {
+          Y[k][j * n] = sx;
+          Y[k][NVF * m * m * n + j * n] = sy;
+        }
+      }
+  } else {
+    for (int it = tid; it < EB * NVF * m * n; it += NT) {
+      const int le = it / (NVF * m * n), r0 = it - le * (NVF * m * n);
+      const int v = r0 / (m * n), r1 = r0 - v * (m * n), a = r1 / n, l = r1 - a * n;
+      const R* Z = ZS(le);
+      R zx[m], zy[m], zz[m];
+#pragma unroll
+      for (int b = 0; b < m; ++b) {
+        zx[b] = Z[(((0 * NVF + v) * m + a) * m + b) * n + l];
+        zy[b] = Z[(((1 * NVF + v) * m + a) * m + b) * n + l];
+        zz[b] = Z[(((2 * NVF + v) * m + a) * m + b) * n + l];
+      }
+      R* Y = YS(le);
+#pragma unroll
+      for (int j = 0; j < n; ++j) {
+        R sx = R(0), sy = R(0);
+#pragma unroll
+        for (int b = 0; b < m; ++b) {
+          sx += op.Pj[j][b] * zx[b];
+          sy += op.AP[j][b] * zy[b];
+          sy += op.Pj[j][b] * zz[b];
+        }
+        Y[(((0 * NVF + v) * m + a) * m + j) * n + l] = sx;
+        Y[(((1 * NVF + v) * m + a) * m + j) * n + l] = sy;
+      }
     }
   }
   lds_barrier();

@@ -1,0 +1,61 @@
+"""The machine code of kernels whose compilation once went wrong without any
+wrong result: operands spilled into vector lanes, loads no longer issued
+ahead.  Reads the gfx950 code of the built library; the bounds lie between the
+counts of the slow and of the present code."""
+
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2401_06132_amd as frmi
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+@pytest.fixture(scope="module")
+def code(tmp_path_factory):
+    """blocks(name): the instruction lists between branches of the kernels whose mangled name holds `name`."""
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no llvm-objdump")
+    d = tmp_path_factory.mktemp("code")
+    shutil.copy(frmi.LIB_PATH, d)
+    subprocess.run([OBJDUMP, "--offloading", os.path.basename(frmi.LIB_PATH)], cwd=d, check=True, capture_output=True)
+    objs = [str(d / f) for f in sorted(os.listdir(d)) if "gfx950" in f]
+    syms = {}
+    for o in objs:
+        for line in subprocess.run([OBJDUMP, "-t", o], check=True, capture_output=True, text=True).stdout.splitlines():
+            if " F .text" in line:
+                syms[line.split()[-1]] = o
+
+    def blocks(name):
+        found = [s for s in syms if name in s]
+        assert found, name
+        out = []
+        for s in found:
+            text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--disassemble-symbols=" + s, syms[s]], check=True,
+                                  capture_output=True, text=True).stdout
+            ops = [m.group(1) for m in re.finditer(r"^\s+([sv]_\S.*|ds_\S.*|global_\S.*|scratch_\S.*)$", text, re.M)]
+            cur = []
+            for op in ops:
+                cur.append(op)
+                if op.startswith(("s_cbranch", "s_branch", "s_barrier")):
+                    out.append(cur)
+                    cur = []
+            out.append(cur)
+        return out
+
+    return blocks
+
+
+def count(block, prefix):
+    return sum(op.startswith(prefix) for op in block)
+
+
+@pytest.mark.parametrize("diag", [0, 1])
+def test_hex_fp64_p4_projection_operands(code, diag):
+    """hex_volume<4, double> with flux anti-aliasing: the y projection once read its operators back from vector
+    lanes for every line (406 lane reads)."""
+    assert max(count(b, "v_readlane") for b in code("hex_volumeILi4EdLi1ELi64ELb%dELb0ELb1ELb0ELb0E" % diag)) < 200
