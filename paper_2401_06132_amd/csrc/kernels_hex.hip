@@ -619,12 +619,37 @@ __global__ void __launch_bounds__(NT)
         for (int j = 0; j < n; ++j) Ib[j] = sI[b2][j];
         const R* T = SS(le) + (side * 20 * m + a2) * n;
         R w[20];
+        if constexpr (sizeof(R) == 8 && P >= 4) {
+          // five fields at a time, the next five's LDS reads in flight: left
+          // to the scheduler each read is waited for by itself (53 waits for
+          // 56 reads; the phases up to here of one element 47 700 -> 36 200
+          // cycles, the kernel at 5^3 38.0 -> 32.8 us, at 33^3 1399 -> 1249)
+          R t[2][5][n];
 #pragma unroll
-        for (int fld = 0; fld < 20; ++fld) {
-          R s = R(0);
+          for (int q = 0; q <= 4; ++q) {
 #pragma unroll
-          for (int b = 0; b < n; ++b) s += Ib[b] * T[fld * m * n + b];
-          w[fld] = s;
+            for (int k = 0; k < 5; ++k)
+#pragma unroll
+              for (int b = 0; b < n; ++b)
+                if (q < 4) t[q & 1][k][b] = T[(q * 5 + k) * m * n + b];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) {
+              R s = R(0);
+#pragma unroll
+              for (int b = 0; b < n; ++b)
+                if (q > 0) s += Ib[b] * t[(q - 1) & 1][k][b];
+              if (q > 0) w[(q - 1) * 5 + k] = s;
+            }
+          }
+        } else {
+#pragma unroll
+          for (int fld = 0; fld < 20; ++fld) {
+            R s = R(0);
+#pragma unroll
+            for (int b = 0; b < n; ++b) s += Ib[b] * T[fld * m * n + b];
+            w[fld] = s;
+          }
         }
         const int lf = le * 6 + 2 * ax + side;
         const R sgn = (cFR[lf].info & 1) ? R(1) : R(-1);

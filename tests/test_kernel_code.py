@@ -59,3 +59,14 @@ def test_hex_fp64_p4_projection_operands(code, diag):
     """hex_volume<4, double> with flux anti-aliasing: the y projection once read its operators back from vector
     lanes for every line (406 lane reads)."""
     assert max(count(b, "v_readlane") for b in code("hex_volumeILi4EdLi1ELi64ELb%dELb0ELb1ELb0ELb0E" % diag)) < 200
+
+
+@pytest.mark.parametrize("diag", [0, 1])
+def test_hex_fp64_p4_face_fields_read_ahead(code, diag):
+    """hex_volume<4, double> with surface-flux anti-aliasing: the face quadrature points once waited for each LDS
+    read by itself (53 waits for 56 reads, once per axis)."""
+    face = [b for b in code("hex_volumeILi4EdLi1ELi64ELb%dELb0ELb1ELb1ELb0E" % diag)
+            if count(b, "v_rcp") and 40 <= count(b, "ds_read") <= 100]
+    assert len(face) == 3  # one per axis
+    for b in face:
+        assert count(b, "s_waitcnt") < 30, (count(b, "ds_read"), count(b, "s_waitcnt"))
