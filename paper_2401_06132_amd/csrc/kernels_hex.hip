@@ -1336,16 +1336,17 @@ template <> struct HexLaunch<4, true> { static constexpr int EB = 1, NT = 64; };
 // waves per SIMD): 0.59 -> 0.51 ms at 48^3 against 7 elements (two
 // workgroups per CU; 5 elements: 0.54 ms).  p = 4: 5 elements per 256
 // threads (245 columns): 1.18 -> 1.13 ms against one-element one-wave
-// groups (curved at 32^3: 0.494 -> 0.486 ms).  The surface-AA and curved
-// kernels keep 7 elements at p = 3, surface AA one-wave groups at p = 4 (18 KB
-// per element: five would leave one workgroup per CU).
+// groups.  The surface-AA and curved kernels keep 7 elements at p = 3 and
+// one-wave groups at p = 4: surface AA needs 18 KB per element (five would
+// leave one workgroup per CU); curved, five are 1.6% faster at 32^3 (0.494 ->
+// 0.486 ms) but 19% slower up to a few hundred elements (5^3 22.3 -> 26.6 us),
+// where the one element of a CU then has its phases in step with four others.
 template <int P, bool DBL, bool AA, bool SAA = false, bool WARP = false>
 struct HexVolLaunch : HexLaunch<P, DBL> {};
 template <> struct HexVolLaunch<3, false, true, false, false> { static constexpr int EB = 6, NT = 256; };
 template <> struct HexVolLaunch<3, false, true, true, false> { static constexpr int EB = 7, NT = 256; };
 template <> struct HexVolLaunch<3, false, true, false, true> { static constexpr int EB = 7, NT = 256; };
 template <> struct HexVolLaunch<4, false, true, false, false> { static constexpr int EB = 5, NT = 256; };
-template <> struct HexVolLaunch<4, false, true, false, true> { static constexpr int EB = 5, NT = 256; };
 
 // elements per workgroup of the disu kernel (256 threads; at 48^3, FP32
 // p = 3: 4 elements 0.099 ms, 8 elements 0.107 ms, 16 elements 0.142 ms)

@@ -70,3 +70,9 @@ def test_hex_fp64_p4_face_fields_read_ahead(code, diag):
     assert len(face) == 3  # one per axis
     for b in face:
         assert count(b, "s_waitcnt") < 30, (count(b, "ds_read"), count(b, "s_waitcnt"))
+
+
+def test_hex_warp_fp32_p4_one_wave_groups(code):
+    """Curved hexahedra, FP32 p = 4: one element per one-wave workgroup (five per four waves were 19% slower on
+    small meshes)."""
+    code("hex_volumeILi4EfLi1ELi64ELb0ELb0ELb1ELb0ELb1E")
