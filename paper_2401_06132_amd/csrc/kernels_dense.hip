@@ -642,6 +642,34 @@ __device__ __forceinline__ void mf_acc(typename MfVec<R>::T& acc, const R* __res
   for (int ks = 0; ks < KS; ++ks) acc = MfVec<R>::mfma(a[ks], b[4 * ks * bs], acc);
 }
 
+// The three products over K = (direction, k-step) that share an accumulator,
+// for operators that fill more than 32 registers per direction (FP64 pyramids
+// p = 4, 64): groups of eight values, the next group's loads in flight over
+// this group's k-steps.  Left to the scheduler, most values are loaded right
+// before their k-step and waited for: the projection of one element 19 100
+// cycles (10 700 when the tile index was not yet scalar), the kernel at 17^3
+// cells 1506 -> 1424 us, at 2^3 25.2 -> 21.3.
+template <int KS, typename R>
+__device__ __forceinline__ void mf_acc3(typename MfVec<R>::T& acc, const R* __restrict__ Ap, const R* bcol, int bs,
+                                        int lane) {
+  constexpr int K = 3 * KS, G = 8, NG = (K + G - 1) / G;
+  const R* b = bcol + (lane >> 4) * bs;
+  R a[2][G];
+#pragma unroll
+  for (int g = 0; g <= NG; ++g) {
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+      if (g * G + i < K) a[g & 1][i] = Ap[(g * G + i) * 64 + lane];
+    __builtin_amdgcn_sched_barrier(0x100);  // LDS reads may cross
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      const int k = (g - 1) * G + i;
+      if (k >= 0 && k < K) acc = MfVec<R>::mfma(a[(g - 1) & 1][i], b[4 * (k % KS) * bs + 4 * (k / KS)], acc);
+    }
+    __builtin_amdgcn_sched_barrier(0x100);
+  }
+}
+
 // The same product in two steps, for a wave that applies one operator tile
 // to several column tiles: the tile's KS values of this lane into
 // registers, then the k-steps against one column
@@ -1150,9 +1178,13 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MfLean<
       const int le = ok ? div_small<NVF>(j) : EB - 1, v = ok ? V0 + j - NVF * le : V0;
       const R* Ap = ops + C::O_PAP + mt * 3 * C::KSQ * 64;
       V4 acc = {R(0), R(0), R(0), R(0)};
+      if constexpr (C::KSQ * int(sizeof(R)) / 4 > 32) {
+        mf_acc3<C::KSQ>(acc, Ap, U2(le) + v - 1, LDW, lane);
+      } else {
 #pragma unroll
-      for (int d = 0; d < 3; ++d)
-        mf_acc<C::KSQ>(acc, Ap + d * C::KSQ * 64, U2(le) + 4 * d + v - 1, LDW, lane);
+        for (int d = 0; d < 3; ++d)
+          mf_acc<C::KSQ>(acc, Ap + d * C::KSQ * 64, U2(le) + 4 * d + v - 1, LDW, lane);
+      }
       const int e = e0 + le;
       if (ok && e < E)
 #pragma unroll

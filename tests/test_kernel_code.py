@@ -76,3 +76,12 @@ def test_hex_warp_fp32_p4_one_wave_groups(code):
     """Curved hexahedra, FP32 p = 4: one element per one-wave workgroup (five per four waves were 19% slower on
     small meshes)."""
     code("hex_volumeILi4EfLi1ELi64ELb0ELb0ELb1ELb0ELb1E")
+
+
+def test_pyr_fp64_p4_projection_loads_ahead(code):
+    """dense_volume_mf<pyramid, 4, double> with flux anti-aliasing: the projection once waited for most operator
+    loads right after issuing them."""
+    proj = [b for b in code("dense_volume_mfILi3ELi4EdLi1ELi256ELb1E") if count(b, "v_mfma") >= 90]
+    assert len(proj) == 1
+    waits = [op for op in proj[0] if op.startswith("s_waitcnt") and "vmcnt(0)" in op]
+    assert len(waits) < 10, len(waits)
