@@ -29,7 +29,11 @@ namespace fr {
 
 typedef float mf4v __attribute__((ext_vector_type(4)));
 
-// one chunk: c + (chunk abid of a) * b; abid must fold to a constant
+// never defined: a call that is left after constant folding ends the compilation
+__device__ __attribute__((error("mf4: the chunk must be a constant below 16 (CBSZ = 3: 8)"))) void mf4_bad_chunk();
+
+// one chunk: c + (chunk abid of a) * b; abid must fold to a constant below 16
+// (CBSZ = 3: 8), any other does not compile
 template <int CBSZ = 4>
 __device__ __forceinline__ mf4v mf4(float a, float b, mf4v c, int abid) {
 #define FR_MF4(i) \
@@ -41,6 +45,7 @@ __device__ __forceinline__ mf4v mf4(float a, float b, mf4v c, int abid) {
     switch (abid) { FR_MF4(8) FR_MF4(9) FR_MF4(10) FR_MF4(11) FR_MF4(12) FR_MF4(13) FR_MF4(14) FR_MF4(15) }
   }
 #undef FR_MF4
+  mf4_bad_chunk();
   return c;
 }
 
@@ -54,8 +59,9 @@ struct Mf4Op {
 #pragma unroll
     for (int i = 0; i < NREG; ++i) a[i] = tab[i * 64 + lane];
   }
-  // acc[t] += rows of column k times x
+  // acc[t] += rows of column k < K times x
   __device__ __forceinline__ void col(int k, float x, mf4v (&acc)[T]) const {
+    if (k < 0 || k >= K) mf4_bad_chunk();
 #pragma unroll
     for (int t = 0; t < T; ++t) acc[t] = mf4(a[(k * T + t) / 16], x, acc[t], (k * T + t) % 16);
   }
