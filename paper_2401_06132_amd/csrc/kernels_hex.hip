@@ -82,12 +82,6 @@ __device__ __forceinline__ void grid_point(int ax, R xi_ax, R ta, R tb, R& x, R&
 template <int P>
 struct HexCfg {
   static constexpr int n = P + 1, m = P + 3, NU = n * n * n, NFP = n * n;
-  static constexpr int SZ_X = 20 * NU;  // state (5) + gradients (15)
-  static constexpr int SZ_J = 30 * NFP; // jumps C - u^f, 6 faces x 5 vars
-  static constexpr int SZ_Z = 15 * m * m * n;
-  static constexpr int SZ_A = (SZ_X + SZ_J > SZ_Z) ? SZ_X + SZ_J : SZ_Z;
-  static constexpr int SZ_T1 = 20 * m * n * n;
-  static constexpr int PER_ELEM = SZ_A + SZ_T1;
 };
 
 // index of the point with coordinate index i along axis ax and tangential
@@ -283,8 +277,7 @@ struct HexVol {
   // variables whose flux is projected: LIN leaves out the mass flux (its
   // divergence is L(rho v), formed by the disu kernel)
   static constexpr int NVF = LIN ? 4 : 5, V0 = 5 - NVF;
-  static constexpr int SZ_X = 20 * NU, SZ_Y = 2 * NVF * m * n * n;
-  static constexpr int SZ_A = SZ_X > SZ_Y ? SZ_X : SZ_Y;
+  static constexpr int SZ_A = 20 * NU;
   // x-interpolated fields T1 [20][m][TPS]; at p = 4 the rows of n^2 are
   // padded to n^2 + 1 so that the quadrature columns of a wave read
   // different banks (measured at 48^3: 1% faster in FP32, 4% in FP64; at

@@ -17,7 +17,6 @@
 // solution point t + NT k; faces 0/1 = zeta -1/+1 (triangle nodes), faces
 // 2/3/4 = edges eta=-1, xi+eta=0, xi=-1 (GL points along the edge x GL in zeta,
 // index i + n k).
-#include <type_traits>
 
 #include "fr_device.h"
 #include "fr_kernels.h"
@@ -43,9 +42,8 @@ struct PrismTriOps {
   R Tedge[3][n][NT];          // nodal basis at the GL points of each edge
   R LiftEdge[3][NT][n];       // DG lifting of an edge point into the plane
 };
-// the device table: the operators, then the triangle nodes and conical
-// quadrature points (needed by curved prisms only; the volume kernel stages
-// them in LDS only then, so the affine kernels keep their LDS size)
+// the device table: the operators (staged in LDS by prism_volume), then the
+// triangle nodes and conical quadrature points (needed by curved prisms only)
 template <int P, typename R>
 struct PrismTri : PrismTriOps<P, R> {
   static constexpr int NT = PrismTriOps<P, R>::NT, NTQ = PrismTriOps<P, R>::NTQ;
@@ -95,12 +93,6 @@ struct PrismCfg {
   static constexpr int PPE = 2 * NT + 3 * NFP;
   __host__ __device__ static constexpr int fsz(int f) { return f < 2 ? NT : NFP; }
   __host__ __device__ static constexpr int foff(int f) { return f < 2 ? f * NT : 2 * NT + (f - 2) * NFP; }
-  static constexpr int SZ_X = 20 * NU;
-  static constexpr int SZ_J = 25 * NFP;  // 5 faces x 5 variables
-  static constexpr int SZ_Z = 15 * NTQ * n;
-  static constexpr int SZ_A = (SZ_X + SZ_J > SZ_Z) ? SZ_X + SZ_J : SZ_Z;
-  static constexpr int SZ_T1 = 20 * n * NTQ;
-  static constexpr int PER_ELEM = SZ_A + SZ_T1;
 };
 
 // reference unit normals of the three quadrilateral faces (xi, eta components)
@@ -297,12 +289,6 @@ struct PrismVol {
   static constexpr int SZ_B1 = SZ_B0 > SZ_J ? SZ_B0 : SZ_J;
   static constexpr int SZ_B = SZ_B1 > SZ_EF ? SZ_B1 : SZ_EF;
   static constexpr int PER_ELEM = SZ_A + SZ_B;
-  // with T1 and Z over region A (TOX): the largest of A + (J, EF, S), T1, Z
-  static constexpr int per_elem_tox(bool SAA) {
-    const int b0 = SAA && SZ_S > SZ_JE ? SZ_S : SZ_JE;
-    const int t = SZ_T1 > SZ_Z ? SZ_T1 : SZ_Z;
-    return SZ_A + b0 > t ? SZ_A + b0 : t;
-  }
   // surface-flux anti-aliasing, one round per face kind: the 20 fields at
   // the two triangles' nodes [2][20][NTN] or along one quadrilateral's first
   // axis at GL(m) [20][m][n] (offset 0); the viscous flux at the face
@@ -310,6 +296,9 @@ struct PrismVol {
   static constexpr int SZ_S0 = 40 * NTN > 20 * m * n ? 40 * NTN : 20 * m * n;
   static constexpr int SZ_S = SZ_S0 + (8 * NTQ > 4 * m * m ? 8 * NTQ : 4 * m * m);
   static_assert(SZ_S <= SZ_B, "face quadrature staging fits region B");
+  // with T1 and Z over region A (TOX): the largest of A + (J, S), T1, Z
+  static constexpr int SZ_JS = SZ_S > SZ_JE ? SZ_S : SZ_JE;
+  static constexpr int PER_ELEM_TOX = SZ_A + SZ_JS > SZ_B0 ? SZ_A + SZ_JS : SZ_B0;
 };
 
 // sum of a value over an adjacent lane pair (lanes 2i, 2i+1), both lanes get
@@ -325,10 +314,12 @@ __device__ __forceinline__ double pair_sum(double x) {
   return x + __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// AA: flux anti-aliasing; without it the flux is evaluated at the solution
+// The affine volume group of the two settings that prism_volume_mf and
+// prism_volume_d (flux anti-aliasing alone; curved elements) do not cover.
+// Without AA the flux is evaluated at the solution
 // points and its divergence is taken in strong form, (M1 - M3 M2) F~: the
 // derivative blocks minus the lifted normal flux interpolated to the faces.
-// SAA: surface-flux anti-aliasing (built with AA only).  The face quadrature
+// AA: flux and surface-flux anti-aliasing.  The face quadrature
 // rules are the volume rule's factors: the conical triangle rule on the two
 // triangles and GL(m)^2 on the quadrilaterals.  As for hexahedra, each side
 // evaluates its normal viscous flux at the face quadrature points and stores
@@ -336,15 +327,14 @@ __device__ __forceinline__ double pair_sum(double x) {
 // (M_T the triangle mass matrix; lifting the projection reproduces the
 // quadrature-point lifting because the rule integrates M_T exactly) and
 // P x P on a quadrilateral.
-template <int P, typename R, int EB, int NT_, bool BT, bool AA, bool SAA, bool WARP>
+template <int P, typename R, int EB, int NT_, bool BT, bool AA>
 __global__ void __launch_bounds__(NT_)
     prism_volume(const Seg one, const BlkRef* __restrict__ bt, const Seg* __restrict__ segs, const bool from_ust,
                  const PrismOps<P, R> op, const PrismTri<P, R>* __restrict__ tri_g, const Gas<R> g,
                  const double eref, const double rho0) {
-  // LIN: the mass flux's divergence and the linear energy-flux part come
-  // from the disu kernel's L(rho v) (affine elements only)
-  constexpr bool LIN = !WARP;
-  using C = PrismVol<P, LIN>;
+  // the mass flux's divergence and the linear energy-flux part come from the
+  // disu kernel's L(rho v)
+  using C = PrismVol<P, true>;
   constexpr int n = C::n, m = C::m, NTN = C::NTN, NTQ = C::NTQ, NU = C::NU, NFP = C::NFP;
   constexpr int NVF = C::NVF, V0 = C::V0;
   using F = PrismCfg<P>;  // face array layout
@@ -356,10 +346,9 @@ __global__ void __launch_bounds__(NT_)
   // which are dead after the plane sweep (FP64 at p = 4 keeps them after
   // region A: the plane values held in registers across the barrier spill)
   constexpr bool TOX = !(P >= 4 && sizeof(R) == 8);
-  constexpr int PE = AA ? (TOX ? C::per_elem_tox(SAA) : C::PER_ELEM) : C::SZ_A + (PL ? C::SZ_JE : C::SZ_J);
+  constexpr int PE = AA ? (TOX ? C::PER_ELEM_TOX : C::PER_ELEM) : C::SZ_A + (PL ? C::SZ_JE : C::SZ_J);
   static_assert(2 * EB * NTQ <= NT_, "two threads per quadrature column");
-  using TriL = typename std::conditional<WARP, PrismTri<P, R>, PrismTriOps<P, R>>::type;
-  __shared__ TriL tri;
+  __shared__ PrismTriOps<P, R> tri;
   __shared__ R smem[EB * PE];
   __shared__ R sMet[EB][10];
   int e0;
@@ -381,7 +370,7 @@ __global__ void __launch_bounds__(NT_)
 
   // phase 0: operator tables, state (reference form), metrics, neighbour states
   {
-    constexpr int NW = sizeof(TriL) / sizeof(R);
+    constexpr int NW = sizeof(tri) / sizeof(R);
     const R* src = reinterpret_cast<const R*>(tri_g);
     R* dst = reinterpret_cast<R*>(&tri);
     for (int it = tid; it < NW; it += NT_) dst[it] = src[it];
@@ -402,14 +391,6 @@ __global__ void __launch_bounds__(NT_)
     for (int k = 0; k < 4; ++k) sFG[it][k] = fgeo[4 * slot + k];
   }
   for (int it = tid; it < sg.nperm * NFP; it += NT_) sPerm[it] = perms[it];
-  __shared__ R sV[WARP ? EB : 1][18];  // curved: element vertices
-  if constexpr (WARP) {
-    const R* __restrict__ vx = (const R*)sg.verts;
-    for (int it = tid; it < EB * 18; it += NT_) {
-      const int le = it / 18;
-      sV[le][it - le * 18] = vx[e0 + le < E ? (size_t)e0 * 18 + it : 0];
-    }
-  }
   for (int it = tid; it < EB * 10; it += NT_) {
     const int le = it / 10, k = it - le * 10, e = e0 + le;
     sMet[le][k] = met[e < E ? (size_t)e * 10 + k : 0];
@@ -610,21 +591,10 @@ __global__ void __launch_bounds__(NT_)
     const int le = it / NU, s = it - le * NU;
     R* X = XS(le);
     R M[3][3];  // M[d][c] = (J^-1)_{dc}
-    if constexpr (WARP) {
-      const int t = s % NTN, k = s / NTN;
-      R S[3][3], det;
-      wedge_metric(&sV[le][0], tri.nodes[t][0], tri.nodes[t][1], psel(op.x, k), S, det);
-      const R id = R(1) / det;
 #pragma unroll
-      for (int d = 0; d < 3; ++d)
+    for (int d = 0; d < 3; ++d)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) M[d][c] = S[d][c] * id;
-    } else {
-#pragma unroll
-      for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) M[d][c] = sMet[le][3 * d + c];
-    }
+      for (int c = 0; c < 3; ++c) M[d][c] = sMet[le][3 * d + c];
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       const R g0 = X[(5 + v) * NU + s], g1 = X[(10 + v) * NU + s], g2 = X[(15 + v) * NU + s];
@@ -634,7 +604,7 @@ __global__ void __launch_bounds__(NT_)
   }
   lds_barrier();
 
-  if constexpr (SAA) {
+  if constexpr (AA) {
     // phase 4a with surface-flux anti-aliasing.  Triangle round: S1 the 20
     // fields at both triangles' nodes (zeta lines), S2 T_q to the
     // triangle quadrature points and n . f^v there, S3 P_T back to the nodes.
@@ -832,19 +802,8 @@ __global__ void __launch_bounds__(NT_)
       for (int side = 0; side < 2; ++side) {
         const R* w = side ? fp : fm;
         const int lf = le * 5 + side, po = sg.po_base + e * F::PPE + side * NTN;
-        R nn[3];
-        if constexpr (WARP) {
-          // own outward unit normal: +-S_zeta / |S_zeta| at the triangle node
-          R S[3][3], det;
-          wedge_metric(&sV[le][0], tri.nodes[t][0], tri.nodes[t][1], side ? R(1) : R(-1), S, det);
-          const R im = rcp(sqrt(S[2][0] * S[2][0] + S[2][1] * S[2][1] + S[2][2] * S[2][2]));
-#pragma unroll
-          for (int c = 0; c < 3; ++c) nn[c] = (side ? im : -im) * S[2][c];
-        } else {
-          const R sgn = (sFR[lf].info & 1) ? R(1) : R(-1);
-#pragma unroll
-          for (int c = 0; c < 3; ++c) nn[c] = sgn * sFG[lf][c];
-        }
+        const R sgn = (sFR[lf].info & 1) ? R(1) : R(-1);
+        const R nn[3] = {sgn * sFG[lf][0], sgn * sFG[lf][1], sgn * sFG[lf][2]};
         R u[5], q[3][5], V[4];
 #pragma unroll
         for (int v = 0; v < 5; ++v) {
@@ -859,24 +818,8 @@ __global__ void __launch_bounds__(NT_)
     } else {
       const int r1 = r0 - NV_TRI, ed = r1 / (n * n), r2 = r1 - ed * (n * n), k = r2 / n, i = r2 - k * n;
       const int lf = le * 5 + 2 + ed, po = sg.po_base + e * F::PPE + F::foff(2 + ed);
-      R nn[3];
-      if constexpr (WARP) {
-        // own outward unit normal: (nx S_xi + ny S_eta) normalised at the edge point
-        R xi, eta, nx, ny, S[3][3], det;
-        edge_point(ed, psel(op.x, i), xi, eta);
-        edge_normal<R>(ed, nx, ny);
-        wedge_metric(&sV[le][0], xi, eta, psel(op.x, k), S, det);
-        R vv[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) vv[c] = nx * S[0][c] + ny * S[1][c];
-        const R im = rcp(sqrt(vv[0] * vv[0] + vv[1] * vv[1] + vv[2] * vv[2]));
-#pragma unroll
-        for (int c = 0; c < 3; ++c) nn[c] = im * vv[c];
-      } else {
-        const R sgn = (sFR[lf].info & 1) ? R(1) : R(-1);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) nn[c] = sgn * sFG[lf][c];
-      }
+      const R sgn = (sFR[lf].info & 1) ? R(1) : R(-1);
+      const R nn[3] = {sgn * sFG[lf][0], sgn * sFG[lf][1], sgn * sFG[lf][2]};
       R u[5], q[3][5], V[4];
 #pragma unroll
       for (int fld = 0; fld < 20; ++fld) {
@@ -1019,7 +962,7 @@ __global__ void __launch_bounds__(NT_)
 #pragma unroll
         for (int t = 0; t < NTN; ++t) {
           R acc = XS(le)[v * NU + t + NTN * k];
-          if (LIN && v == 4) acc += g.kap * Rp[(size_t)e * 5 * NU + t + NTN * k];  // kap L(rho v)
+          if (v == 4) acc += g.kap * Rp[(size_t)e * 5 * NU + t + NTN * k];  // kap L(rho v)
 #pragma unroll
           for (int c = 0; c < NTN; ++c) acc += tri.Dxi[t][c] * fx[c] + tri.Deta[t][c] * fy[c];
 #pragma unroll
@@ -1031,7 +974,7 @@ __global__ void __launch_bounds__(NT_)
       } else {
         const int v = V0 + r0 / NU, s = r0 - (v - V0) * NU, k = s / NTN, t = s - k * NTN;
         R acc = XS(le)[v * NU + s];
-        if (LIN && v == 4) acc += g.kap * Rp[(size_t)e * 5 * NU + s];  // kap L(rho v)
+        if (v == 4) acc += g.kap * Rp[(size_t)e * 5 * NU + s];  // kap L(rho v)
 #pragma unroll
         for (int c = 0; c < NTN; ++c)
           acc += tri.Dxi[t][c] * F[(0 * 5 + v) * NU + c + NTN * k] + tri.Deta[t][c] * F[(1 * 5 + v) * NU + c + NTN * k];
@@ -1132,11 +1075,6 @@ __global__ void __launch_bounds__(NT_)
     for (int d = 0; d < 3; ++d)
 #pragma unroll
       for (int c = 0; c < 3; ++c) S[d][c] = dj * sMet[cle][3 * d + c];
-    R cqx = R(0), cqy = R(0);
-    if constexpr (WARP) {
-      cqx = tri.qp[ctq][0];
-      cqy = tri.qp[ctq][1];
-    }
     // thread `half` takes zeta level kq = 2j + half; the operator entries are
     // selected per lane (no divergent branch); for odd m the surplus level of
     // the odd thread repeats level 2j with zero projection weights
@@ -1163,10 +1101,6 @@ __global__ void __launch_bounds__(NT_)
           q[(fld - 5) / 5][(fld - 5) % 5] = s;
       }
       point_flux(u, q, g, f);
-      if constexpr (WARP) {
-        R det;
-        wedge_metric(&sV[cle][0], cqx, cqy, half ? op.xq[k1] : op.xq[k0], S, det);  // det J J^-1 here
-      }
 #pragma unroll
       for (int d = 0; d < 3; ++d)
 #pragma unroll
@@ -1199,8 +1133,8 @@ __global__ void __launch_bounds__(NT_)
 
   // phase 6: triangle-plane projection-divergence: one (variable, plane) per
   // thread, its 3 N_tq line-projected flux values in registers, operator
-  // entries read from the LDS copy at wave-uniform addresses; LIN: the
-  // energy residual takes kap L(rho v) (row 0, from the disu kernel)
+  // entries read from the LDS copy at wave-uniform addresses;
+  // the energy residual takes kap L(rho v) (row 0, from the disu kernel)
   for (int it = tid; it < EB * NVF * n * SPL; it += NT_) {
     const int le = it / (NVF * n * SPL), r0 = it - le * (NVF * n * SPL), vk = r0 / SPL, h = r0 - vk * SPL;
     const int vv = vk / n, k = vk - vv * n, e = e0 + le, v = vv + V0;
@@ -1217,7 +1151,7 @@ __global__ void __launch_bounds__(NT_)
     for (int j = 0; j < (NTN + SPL - 1) / SPL; ++j) {
       const int t = SPL * j + h;
       if (t < NTN) {
-        R s = (LIN && v == 4) ? g.kap * Rp[(size_t)e * 5 * NU + t + NTN * k] : R(0);
+        R s = v == 4 ? g.kap * Rp[(size_t)e * 5 * NU + t + NTN * k] : R(0);
 #pragma unroll
         for (int tq = 0; tq < NTQ; ++tq) {
           s += tri.APxi[t][tq] * z0[tq];
@@ -1715,7 +1649,7 @@ static void prism_launch(const TypeArgs& a, const int grid[3], hipStream_t st) {
     // surface-flux anti-aliasing is built together with flux anti-aliasing
     // only (the paper's "full AA"); the library rejects it without
     if (a.saa)
-      hipLaunchKernelGGL((prism_volume<P, R, EB, NT, BT, true, true, false>), dim3(grid[K_VOLUME]), dim3(NT), 0, st, a.one,
+      hipLaunchKernelGGL((prism_volume<P, R, EB, NT, BT, true>), dim3(grid[K_VOLUME]), dim3(NT), 0, st, a.one,
                          a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, g, eref, rho0);
     else if (a.aa) {
       if constexpr (dbl)
@@ -1725,7 +1659,7 @@ static void prism_launch(const TypeArgs& a, const int grid[3], hipStream_t st) {
         hipLaunchKernelGGL((prism_volume_mf<P, BT, false>), dim3(grid[K_VOLUME]), dim3(PrismMf<P, true>::NT), 0, st,
                            a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, mft, g, eref, rho0);
     } else
-      hipLaunchKernelGGL((prism_volume<P, R, EB, NT, BT, false, false, false>), dim3(grid[K_VOLUME]), dim3(NT), 0, st,
+      hipLaunchKernelGGL((prism_volume<P, R, EB, NT, BT, false>), dim3(grid[K_VOLUME]), dim3(NT), 0, st,
                          a.one, a.bt[K_VOLUME], a.segs, a.from_ust, op, tri, g, eref, rho0);
   }
   if ((a.stage & 4) && grid[K_SURFACE] > 0) {
