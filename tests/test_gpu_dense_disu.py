@@ -8,9 +8,11 @@ import numpy as np
 import pytest
 
 import paper_2401_06132_amd as frmi
-from oracle.mesh import Mesh
+from oracle.mesh import Mesh, elements_mesh
 from oracle.rhs import Params, rhs as oracle_rhs
 from paper_2401_06132_amd import inputs
+from test_gpu_lds_nan import _staged_rhs_after_nan_fills
+from test_mesh_elements import sheared_case
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -35,5 +37,30 @@ def test_tile_edges(dims, p, kind, prec):
     torch.cuda.synchronize()
     err = np.max([(np.abs(g - ref[t]).max(axis=(0, 2)) / np.abs(ref[t]).max(axis=(0, 2))).astype(np.float64)
                   for g, t in zip(s.split(du.cpu().numpy()), m.types)], axis=0)
+    print("rel err per variable", err, flush=True)
+    assert np.all(err < (1e-12 if prec == "fp64" else 2e-5)), err
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("kind", ["tet", "pyr"])
+@pytest.mark.parametrize("p", [1, 2, 3, 4])
+def test_partial_last_group(p, kind, prec):
+    """18 elements: two whole workgroups of eight and one with two elements, LDS filled with NaN before each
+    kernel group."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("partial group case", p, kind, prec, flush=True)
+    # three cubic cells in a row
+    verts, lat, _ = sheared_case((1, 1, 3), p, kind, A=np.diag([1.0, 1.0, 3.0]))
+    m = elements_mesh(p, verts, lat)
+    U = inputs.element_state([m.upts_coords(t) for t in m.types], seed=18)
+    assert len(U[0]) == 18
+    ref = oracle_rhs(m, {t: u.astype(np.longdouble) for t, u in zip(m.types, U)}, Params(pref=inputs.P0),
+                     dtype=np.longdouble)
+    s = frmi.Solver(None, p, "elements", verts=verts, period=lat, prec=prec, pref=inputs.P0, rho_ref=inputs.RHO0)
+    du = _staged_rhs_after_nan_fills(s, np.concatenate([x.reshape(-1) for x in U]))
+    assert np.all(np.isfinite(du))
+    err = np.max([(np.abs(g - ref[t]).max(axis=(0, 2)) / np.abs(ref[t]).max(axis=(0, 2))).astype(np.float64)
+                  for g, t in zip(s.split(du), m.types)], axis=0)
     print("rel err per variable", err, flush=True)
     assert np.all(err < (1e-12 if prec == "fp64" else 2e-5)), err
