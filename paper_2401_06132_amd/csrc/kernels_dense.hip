@@ -246,8 +246,9 @@ __global__ void __launch_bounds__(NT) dense_disu(const Seg sg, const bool from_u
   }
   lds_barrier();
   // M0: 16 x 16 tiles of (flux points) x (element, variable) columns; the
-  // instruction ignores EXEC, so a column or k past the end reads a valid
-  // value (of the same column: the operator is zero there) and is dropped
+  // instruction ignores EXEC, so a column past the end reads a valid one and
+  // is dropped; k past the end enters as zero (the operator is zero there, but
+  // an infinite value would become a NaN, which the wave speed's maximum drops)
   for (int pr = wave; pr < DD::RT0 * CT; pr += NW) {
     const int rt = pr / CT, col = (pr - rt * CT) * 16 + lj;
     const double* A = ops + DD::O_M0 + rt * DD::KS0 * 64 + lane;
@@ -256,7 +257,8 @@ __global__ void __launch_bounds__(NT) dense_disu(const Seg sg, const bool from_u
 #pragma unroll
     for (int ks = 0; ks < DD::KS0; ++ks) {
       const int k = 4 * ks + lk;
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[ks * 64], B[k < NU ? k : NU - 1], acc, 0, 0, 0);
+      const double b = B[k < NU ? k : NU - 1];
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[ks * 64], k < NU ? b : 0.0, acc, 0, 0, 0);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -302,7 +304,8 @@ __global__ void __launch_bounds__(NT) dense_disu(const Seg sg, const bool from_u
 #pragma unroll
     for (int ks = 0; ks < DD::KS1; ++ks) {
       const int k = 4 * ks + lk;
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[ks * 64], B[k < 3 * NU ? k : 3 * NU - 1], acc, 0, 0, 0);
+      const double b = B[k < 3 * NU ? k : 3 * NU - 1];
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[ks * 64], k < 3 * NU ? b : 0.0, acc, 0, 0, 0);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {

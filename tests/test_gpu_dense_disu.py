@@ -64,3 +64,23 @@ def test_partial_last_group(p, kind, prec):
                   for g, t in zip(s.split(du), m.types)], axis=0)
     print("rel err per variable", err, flush=True)
     assert np.all(err < (1e-12 if prec == "fp64" else 2e-5)), err
+
+
+@pytest.mark.parametrize("node", [0, -1])
+@pytest.mark.parametrize("kind,p", [("tet", 2), ("tet", 4), ("pyr", 1), ("pyr", 2), ("pyr", 3), ("pyr", 4)])
+def test_infinity_reaches_the_face_values(kind, p, node):
+    """FP64, point counts that are no multiple of the k-steps' four: an infinite energy makes the element's face
+    values infinite, and so the wave speed and every residual of the element not finite, whichever node holds it.
+    The zero padding of the operator must not turn it into a NaN (which a maximum drops)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("infinity case", kind, p, node, flush=True)
+    s = frmi.Solver(3, p, kind, pref=inputs.P0, rho_ref=inputs.RHO0)
+    U = inputs.element_state(s.upts_coords(), seed=21)
+    E = len(U[0])
+    U[0][E // 2, 4, node] = np.inf
+    u = torch.from_numpy(U[0].reshape(-1)).cuda()
+    du = torch.empty_like(u)
+    s.rhs(u, du)
+    torch.cuda.synchronize()
+    assert not np.isfinite(s.split(du.cpu().numpy())[0][E // 2]).any()
