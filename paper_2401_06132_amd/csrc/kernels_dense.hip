@@ -605,11 +605,11 @@ __global__ void __launch_bounds__(NT) dense_volume(const Seg sg, const bool from
 // quadrature values) go through LDS rows; the three directions of the
 // projection-divergence are one product with K concatenated.
 // Bound by instruction issue (single-precision matrix and vector instructions
-// share the ALUs; together busy 83% of the time at tetrahedra p = 3), half of
-// it index arithmetic: with the tile loops on the scalar unit, one flux point
-// per gather item and the constant fluxes formed once in an idle wave,
-// 196 608 tetrahedra p = 3 take 746 us instead of 814, 41 472 pyramids 238
-// instead of 251.
+// share the ALUs; busy 40% and 35% of the time at tetrahedra p = 3).  With the
+// tile loops on the scalar unit, one flux point per gather item and the constant
+// fluxes formed once in an idle wave (870 M -> 546 M vector instructions at
+// 48^3 cells) 196 608 tetrahedra p = 3 take 746 us instead of 814, 41 472
+// pyramids 238 instead of 251.
 typedef float mf4 __attribute__((ext_vector_type(4)));
 typedef double md4 __attribute__((ext_vector_type(4)));
 template <typename R>

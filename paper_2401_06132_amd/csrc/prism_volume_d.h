@@ -15,7 +15,9 @@
 // with the tables in LDS and two lanes per column (three one-wave workgroups
 // per CU at p = 4): 14 858 prisms p = 4 917 -> 424 us, 32^3 cells p = 3
 // 1112 -> 764 us, p = 2 488 -> 294 us, 40^3 p = 1 260 -> 187 us; curved, 24^3
-// p = 3 506 -> 366 us, 20^3 p = 4 1202 -> 508 us.
+// p = 3 506 -> 366 us, 20^3 p = 4 1202 -> 508 us.  Bound by latency: three
+// two-wave workgroups per CU at p = 4 (49 KB of LDS each), a vector instruction
+// every 15 cycles and SIMD, 57% of the waves' time waiting.
 namespace fr {
 
 // one row of K operator entries in scalar registers

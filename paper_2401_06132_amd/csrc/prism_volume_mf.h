@@ -21,12 +21,14 @@
 // The operators come from L2 as packed chunks, a register per 16 chunks, so
 // no table sits in LDS, and every LDS array lies over the dead one before it:
 // 26 KB per four elements at p = 3 (six two-wave workgroups per CU) and 52 KB
-// per five at p = 4 (three four-wave ones), three waves per SIMD at both.
-// Bound by instruction issue: vector and matrix pipes together busy 77% (p = 3)
-// and 70% (p = 4) of the time.  Measured (volume group, MI355X): 48^3 cells
-// p = 3 1474 -> 750 us, 262 144 prisms p = 4 5586 -> 1795 us, 32 768 curved
-// prisms p = 3 251 -> 141 us, against the vector kernel with its operator
-// tables in LDS (8 and 7 waves per CU); with EF and the face records in LDS of
+// per five at p = 4 (three four-wave ones), three waves per SIMD at both; at
+// p = 4 that costs 8 to 10 spilled registers (curved 17), 42% of what the kernel
+// writes to memory, and is faster all the same.  Bound by instruction issue:
+// vector and matrix instructions together busy 74% (p = 3) and 66% (p = 4) of
+// the time.  Measured (volume group, MI355X): 48^3 cells p = 3 1474 -> 750 us,
+// 262 144 prisms p = 4 5586 -> 1795 us, 32 768 curved prisms p = 3 251 -> 141
+// us, against the vector kernel with its operator tables in LDS (8 and 7 waves
+// per CU); with EF and the face records in LDS of
 // their own (five and two workgroups per CU) 817, 2133 and 155 us.
 namespace fr {
 
