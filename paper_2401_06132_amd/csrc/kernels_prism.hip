@@ -1456,6 +1456,56 @@ __global__ void __launch_bounds__(NT_)
   }
 }
 
+// What prism_volume_mf and prism_volume_d share.
+
+// curved: the physical gradient q = J^-T q~ (eq. FR-gradcoru) at solution
+// point s, in place in X [20][NU]
+template <int P, typename R>
+__device__ __forceinline__ void wedge_gradient(const PrismOps<P, R>& op, const PrismTri<P, R>* __restrict__ tri,
+                                               const R* verts, int s, R* X) {
+  constexpr int NT = PrismCfg<P>::NT, NU = PrismCfg<P>::NU;
+  const int t = s % NT, k = s / NT;
+  R S[3][3], det;
+  wedge_metric(verts, tri->nodes[t][0], tri->nodes[t][1], psel(op.x, k), S, det);
+  const R id = R(1) / det;
+#pragma unroll
+  for (int v = 0; v < 5; ++v) {
+    const R g0 = X[(5 + v) * NU + s], g1 = X[(10 + v) * NU + s], g2 = X[(15 + v) * NU + s];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) X[(5 + c * 5 + v) * NU + s] = S[0][c] * id * g0 + S[1][c] * id * g1 + S[2][c] * id * g2;
+  }
+}
+
+// curved: own outward unit normal at node t of triangle face `side`,
+// +-S_zeta / |S_zeta|
+template <int P, typename R>
+__device__ __forceinline__ void wedge_tri_normal(const PrismTri<P, R>* __restrict__ tri, const R* verts, int t, int side,
+                                                 R nn[3]) {
+  R S[3][3], det;
+  wedge_metric(verts, tri->nodes[t][0], tri->nodes[t][1], side ? R(1) : R(-1), S, det);
+  const R im = rcp(sqrt(S[2][0] * S[2][0] + S[2][1] * S[2][1] + S[2][2] * S[2][2]));
+#pragma unroll
+  for (int c = 0; c < 3; ++c) nn[c] = (side ? im : -im) * S[2][c];
+}
+
+// the same at point r of the quadrilateral face on edge ed: (nx S_xi + ny
+// S_eta) normalised at the edge point
+template <int P, typename R>
+__device__ __forceinline__ void wedge_quad_normal(const PrismOps<P, R>& op, const R* verts, int ed, int r, R nn[3]) {
+  constexpr int n = P + 1;
+  const int k = r / n, i = r - k * n;
+  R xi, eta, nx, ny, S[3][3], det;
+  edge_point(ed, psel(op.x, i), xi, eta);
+  edge_normal<R>(ed, nx, ny);
+  wedge_metric(verts, xi, eta, psel(op.x, k), S, det);
+  R vv[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) vv[c] = nx * S[0][c] + ny * S[1][c];
+  const R im = rcp(sqrt(vv[0] * vv[0] + vv[1] * vv[1] + vv[2] * vv[2]));
+#pragma unroll
+  for (int c = 0; c < 3; ++c) nn[c] = im * vv[c];
+}
+
 }  // namespace fr
 #include "prism_volume_d.h"
 #include "prism_volume_mf.h"

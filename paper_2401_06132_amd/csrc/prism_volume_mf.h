@@ -318,18 +318,8 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
   lds_barrier();
   if constexpr (WARP) {
     for (int it = tid; it < EB * NU; it += NT_) {
-      const int le = it / NU, s = it - le * NU, t = s % NTN, k = s / NTN;
-      R* X = XS(le);
-      R S[3][3], det;
-      wedge_metric(&sV[le][0], tri->nodes[t][0], tri->nodes[t][1], psel(op.x, k), S, det);
-      const R id = R(1) / det;
-#pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        const R g0 = X[(5 + v) * NU + s], g1 = X[(10 + v) * NU + s], g2 = X[(15 + v) * NU + s];
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-          X[(5 + c * 5 + v) * NU + s] = S[0][c] * id * g0 + S[1][c] * id * g1 + S[2][c] * id * g2;
-      }
+      const int le = it / NU;
+      wedge_gradient<P, R>(op, tri, &sV[le][0], it - le * NU, XS(le));
     }
     lds_barrier();
   }
@@ -377,12 +367,7 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
       const int po = sg.po_base + e * F::PPE + side * NTN;
       R nn[3];
       if constexpr (WARP) {
-        // own outward unit normal: +-S_zeta / |S_zeta| at the triangle node
-        R S[3][3], det;
-        wedge_metric(&sV[le][0], tri->nodes[t][0], tri->nodes[t][1], side ? R(1) : R(-1), S, det);
-        const R im = rcp(sqrt(S[2][0] * S[2][0] + S[2][1] * S[2][1] + S[2][2] * S[2][2]));
-#pragma unroll
-        for (int c = 0; c < 3; ++c) nn[c] = (side ? im : -im) * S[2][c];
+        wedge_tri_normal(tri, &sV[le][0], t, side, nn);
       } else {
         const R sgn = (FR(le)[side].info & 1) ? R(1) : R(-1);
 #pragma unroll
@@ -421,18 +406,7 @@ __global__ void __launch_bounds__((PrismMf<P, !WARP>::NT)) __attribute__((amdgpu
     const int po = sg.po_base + e * F::PPE + F::foff(2 + ed);
     R nn[3];
     if constexpr (WARP) {
-      // own outward unit normal: (nx S_xi + ny S_eta) normalised at the edge point
-      const int k = r2 / n, i = r2 - k * n;
-      R xi, eta, nx, ny, S[3][3], det;
-      edge_point(ed, psel(op.x, i), xi, eta);
-      edge_normal<R>(ed, nx, ny);
-      wedge_metric(&sV[le][0], xi, eta, psel(op.x, k), S, det);
-      R vv[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) vv[c] = nx * S[0][c] + ny * S[1][c];
-      const R im = rcp(sqrt(vv[0] * vv[0] + vv[1] * vv[1] + vv[2] * vv[2]));
-#pragma unroll
-      for (int c = 0; c < 3; ++c) nn[c] = im * vv[c];
+      wedge_quad_normal(op, &sV[le][0], ed, r2, nn);
     } else {
       const R sgn = (FR(le)[2 + ed].info & 1) ? R(1) : R(-1);
 #pragma unroll
